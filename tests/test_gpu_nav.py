@@ -69,3 +69,27 @@ def test_dvl_matches_oracle(T, N, min_beams, sigma_v):
     # every status occurs in the larger cases
     if T * N > 1000:
         assert set(np.unique(st).tolist()) == {0, 1, 2}
+
+
+@pytest.mark.parametrize("N", [1, 63, 64, 65, 200])
+@pytest.mark.parametrize("T, dt", [(1, 0.01), (31, 0.2), (32, 0.01), (33, 0.2), (64, 0.01), (161, 0.02)])
+def test_dvl_slabs_and_instance_groups(T, N, dt):
+    """Tick counts around the kernel's slabs of 32 (first, last and partial
+    slabs, three buffers in turn), instance counts around its groups of 64;
+    ticks of 0.2 s make every tick due, so each wave's list is full."""
+    import torch
+    import paper_2503_01074_amd as osm
+    rs = np.random.default_rng(1000 * T + N)
+    t = np.cumsum(rs.uniform(0.9 * dt, 1.1 * dt, T))
+    _, ranges, vel = _dvl_case(T, N, 77 * T + N)
+    cfg = DvlConfig(sigma_v=0.02, pings_per_output=1.0, seed_lo=5, seed_hi=6)
+    vo, st = osm.dvl(torch.as_tensor(t).cuda(), torch.as_tensor(ranges).cuda(), torch.as_tensor(vel).cuda(),
+                     sigma_v=0.02, pings_per_output=1.0, seed=(5, 6))
+    torch.cuda.synchronize()
+    want_v, want_s = oracle.dvl(t, ranges, vel, cfg)
+    np.testing.assert_array_equal(st.cpu().numpy(), want_s)
+    vo = vo.cpu().numpy()
+    good = want_s == 1
+    assert np.all(np.isnan(vo[~good]))
+    if good.any():
+        assert_image_close(vo[good], want_v[good], "dvl velocity")
