@@ -184,13 +184,15 @@ struct Builder {
         nodes.emplace_back();
         sah += nb.area() * kCostNode;
         const int r0 = build(b, mid, d + 1);
+        const int split = (int)order.size();
         const int r1 = build(mid, e, d + 1);
         BvhNode &nd = nodes[id];
         store_box(bounds(b, mid), nd.lo0, nd.hi0);
         store_box(bounds(mid, e), nd.lo1, nd.hi1);
         nd.ref[0] = r0;
         nd.ref[1] = r1;
-        nd.pad[0] = nd.pad[1] = 0;
+        nd.split = split;
+        nd.pad = 0;
         return id;
     }
 };

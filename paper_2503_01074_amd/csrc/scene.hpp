@@ -26,11 +26,13 @@ constexpr float kMinDirComponent = 8.67361737988403547e-19f;
 
 __host__ __device__ inline int leaf_ref(int first, int count) { return ~((first << kLeafShift) | (count - 1)); }
 
-// 64 bytes: child 0 box, child 1 box, the two references.
+// 64 bytes: child 0 box, child 1 box, the two references, the triangle slot
+// from which on child 1's triangles are stored (child 0's come before it).
 struct alignas(16) BvhNode {
     float lo0[3], hi0[3], lo1[3], hi1[3];
     int32_t ref[2];
-    int32_t pad[2];
+    int32_t split;
+    int32_t pad;
 };
 static_assert(sizeof(BvhNode) == 64, "node layout");
 

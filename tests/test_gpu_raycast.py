@@ -235,3 +235,46 @@ def test_deepest_hierarchy_full_stack():
     want = _oracle(s, pose, 64, 32, 20.0, sel=sel, fov_az=fa, fov_el=fe)
     n_ok, _ = _compare(got, want, 20.0, sel=sel)
     assert n_ok > 300 and (want["mat"] >= 0).sum() > 300
+
+
+def _grid_plane(n=33, extent=64.0, z=-5.0):
+    """A flat grid of cells split along their diagonals, with edges along y = 0, each triangle its own material."""
+    xs = np.linspace(-0.5 * extent, 0.5 * extent, n)
+    X, Y = np.meshgrid(xs, xs, indexing="ij")
+    v = np.stack([X, Y, np.full_like(X, z)], -1).reshape(-1, 3).astype(np.float32)
+    i = np.arange(n * n).reshape(n, n)
+    a, b, c, d = i[:-1, :-1], i[1:, :-1], i[1:, 1:], i[:-1, 1:]
+    t = np.concatenate([np.stack([a, b, c], -1).reshape(-1, 3), np.stack([a, c, d], -1).reshape(-1, 3)])
+    return v, t.astype(np.int32), np.arange(len(t), dtype=np.int32)
+
+
+@pytest.mark.parametrize("n_beams, n_rays", [(512, 256), (511, 257), (1300, 200), (61, 4001), (4099, 63), (2500, 100)])
+@pytest.mark.parametrize("mesh", ["seabed", "plane"])
+def test_shared_traversal_equals_the_lanes_own(mesh, n_beams, n_rays):
+    """A fine pattern of fewer than 2^18 rays is cast by one traversal per
+    lane; two poses of it in one call pass 2^18 and are cast by one traversal
+    per wave.  Bit for bit the same, ties between triangles that share an edge
+    included: on the plane, the odd patterns' middle beam runs along an edge
+    (and has a zero direction component), and waves straddle the octants."""
+    import torch
+    import paper_2503_01074_amd as osm
+    if mesh == "seabed":
+        sc = W.seabed_scene(n=96, extent=120.0)
+        arrays, pose = (sc.vertices, sc.triangles, sc.tri_mat), W.sonar_pose(height=6.0, pitch_deg=12.0, yaw_deg=90.0)
+        poses = [(pose.pos, pose.rot)]
+    else:
+        arrays = _grid_plane()
+        poses = [(np.zeros(3, np.float32), np.eye(3, dtype=np.float32))]
+    scene = osm.Scene(*arrays)
+    fov = (float(np.float32(2.2)), float(np.float32(0.4)))
+    assert n_beams * n_rays < 2 ** 18 and 64 * fov[0] * fov[1] <= 5e-4 * n_beams * n_rays
+    one = osm.raycast(scene, poses, n_beams, n_rays, *fov, 60.0)[0]
+    k = -(-2 ** 18 // (n_beams * n_rays))
+    many = osm.raycast(scene, poses * k, n_beams, n_rays, *fov, 60.0)
+    torch.cuda.synchronize()
+    hits = one.mat.cpu().numpy()
+    assert (hits >= 0).any() and (hits < 0).any()
+    for h in (many[0], many[-1]):
+        for name in ("x", "y", "z", "nx", "ny", "nz", "mat"):
+            assert torch.equal(getattr(h, name).view(torch.int32), getattr(one, name).view(torch.int32)), name
+    scene.close()
