@@ -208,10 +208,31 @@ int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_row
     int bin_blocks = 0, tile_blocks = 0, tile_b_blocks = 0, fan_blocks = 0, ret_blocks = 0, fant_blocks = 0;
     int row_blocks = 0, max_rows_per_tile = 0;   // range-wise normalisation
     P.off_dldq.assign(n_frames, (size_t)-1);
-    // Bins per thread through the transposed fan operators: one while the
-    // workgroups fit the chip a few times over; more for large batches, where
-    // the per-workgroup costs (frame lookup, pointer loads, partial sums) add up.
+    // Operator rows per thread through the transposed fan operators: one while
+    // the workgroups fit the chip a few times over; two or four for large
+    // batches, where the per-workgroup costs (frame lookup, pointer loads,
+    // partial sums) add up, but only while rows are short: a thread sums its
+    // rows' entries one after the other, and a row has about four entries per
+    // fan pixel per bin.  Measured at 4 frames (1, 2, 4 rows per thread, us;
+    // mirrored operators): 1024^2 bins with 0.17 pixels a bin 33, 30, 31, with
+    // 0.69 34, 37, 52, with 3.7 87, 132, 467; 2048^2 with 0.04 108, 94, 91, with
+    // 0.39 121, 113, 126, with 0.93 149, 149, 202.  Plain operators (half the
+    // gathers a row): 1024^2 with 1.5 52, 51, 78, with 3.7 110, 115, 258.
     int fant_bpt = total_nb >= (16LL << 20) ? 4 : (total_nb >= (2LL << 20) ? 2 : 1);
+    if (backward && fant_bpt > 1) {
+        double px = 0.0;
+        bool mirror = false;
+        for (int i = 0; i < n_frames; ++i) {
+            const int layout = fan_operator_layout(frames[i]);
+            if (layout != 0) px += (double)frames[i].fan_h * frames[i].fan_w;
+            mirror = mirror || layout == 2;
+        }
+        const double per_bin = px / (double)total_nb;
+        if (per_bin > (mirror ? 0.5 : 1.5))
+            fant_bpt = 1;
+        else if (per_bin > 0.2)
+            fant_bpt = 2;
+    }
     if (tune && (tune->fant_bpt == 1 || tune->fant_bpt == 2 || tune->fant_bpt == 4)) fant_bpt = tune->fant_bpt;
     for (int i = 0; i < n_frames; ++i) {
         const oceansim_sonar_frame &fr = frames[i];

@@ -625,6 +625,14 @@ void for_each_entry(const oceansim_sonar_frame &f, const std::vector<HostRec> &r
         }
 }
 
+// Whether two frames have the same fan operator: everything the stencils and
+// the operator's layout are made from (for frames that have one).
+bool same_fan_operator(const oceansim_sonar_frame &a, const oceansim_sonar_frame &b) {
+    return a.fan_h == b.fan_h && a.fan_w == b.fan_w && a.n_range == b.n_range && a.n_azimuth == b.n_azimuth &&
+           a.r_min == b.r_min && a.r_max == b.r_max && a.fov_az == b.fov_az &&
+           fan_operator_layout(a) == fan_operator_layout(b);
+}
+
 // Stencils of the frames that need an operator, then the operators; the
 // plan's own stencil memory is released afterwards (the forward pass then
 // saves none).
@@ -640,6 +648,17 @@ int build_fan_transposes(oceansim_plan *p, hipStream_t st) {
             need.push_back(i);
         }
     if (need.empty()) return OCEANSIM_OK;
+    // frames of one fan geometry (a batch from one sensor) share one operator:
+    // built once, held once, and read from the caches by all frames but the first
+    std::vector<size_t> same(need.size());
+    for (size_t k = 0; k < need.size(); ++k) {
+        same[k] = k;
+        for (size_t j = 0; j < k; ++j)
+            if (same[j] == j && same_fan_operator(p->sonar[need[j]], p->sonar[need[k]])) {
+                same[k] = j;
+                break;
+            }
+    }
     SonarPlan fp;
     int rc = plan_sonar(p->sonar.data(), n, p->n_srows, p->n_mat, false, fp, nullptr, true);
     if (rc) return rc;
@@ -652,6 +671,7 @@ int build_fan_transposes(oceansim_plan *p, hipStream_t st) {
         e = sonar_fan_stencils_table(reinterpret_cast<const SonarDev *>(ws + fp.off_table), n, fp.grid, st);
     std::vector<std::vector<HostRec>> recs(need.size());
     for (size_t k = 0; k < need.size() && e == hipSuccess; ++k) {
+        if (same[k] != k) continue;
         const oceansim_sonar_frame &f = p->sonar[need[k]];
         recs[k].resize((size_t)f.fan_h * ((f.fan_w + 1) / 2));
         e = hipMemcpyAsync(recs[k].data(), f.fan_stencil, recs[k].size() * sizeof(HostRec), hipMemcpyDeviceToHost,
@@ -666,6 +686,7 @@ int build_fan_transposes(oceansim_plan *p, hipStream_t st) {
     size_t bytes = 0;
     std::vector<size_t> off_ptr(need.size()), off_ent(need.size());
     for (size_t k = 0; k < need.size(); ++k) {
+        if (same[k] != k) continue;
         const oceansim_sonar_frame &f = p->sonar[need[k]];
         const bool mirror = fan_operator_layout(f) == 2;
         const int n_az = f.n_azimuth, ncol = mirror ? (n_az + 1) / 2 : n_az;
@@ -706,6 +727,11 @@ int build_fan_transposes(oceansim_plan *p, hipStream_t st) {
     e = hipMalloc(&p->fant_mem, bytes);
     if (e != hipSuccess) return hip_fail(e, "fan operator memory");
     for (size_t k = 0; k < need.size() && e == hipSuccess; ++k) {
+        if (same[k] != k) {
+            p->fant_ptr[need[k]] = p->fant_ptr[need[same[k]]];
+            p->fant_ent[need[k]] = p->fant_ent[need[same[k]]];
+            continue;
+        }
         e = hipMemcpyAsync(p->fant_mem + off_ptr[k], ptr[k].data(), sizeof(int) * ptr[k].size(),
                            hipMemcpyHostToDevice, st);
         if (e == hipSuccess && !ent[k].empty())

@@ -199,3 +199,54 @@ def test_plan_fan_transpose_large_batches(n_frames, n_bins, block_bins, mixed, o
     o_refl, o_par, c_refl, c_par = _oracle(frames, refl, gpol, gfan)
     assert_grad_cond(g_refl, o_refl, c_refl, what="refl")
     assert_grad_cond(g_par[0, :5], o_par[0], c_par[0], what="params")
+
+
+@pytest.mark.parametrize("fan", [(96, 200), (96, 201)])
+def test_frames_of_one_geometry_share_an_operator(fan):
+    """Frames of the same fan geometry read one operator; one that differs in
+    a single field (range, grid or fan) has its own."""
+    st = W.Stream(8600 + fan[1], 0)
+    H, Wd = fan
+    frames = [_frame(st, 60, 50, H, Wd, 2000, frame_id=0), _frame(st, 60, 50, H, Wd, 1500, frame_id=1, mode=W.SPECKLE_GAMMA),
+              _frame(st, 60, 50, H, Wd, 1000, frame_id=2, r_max=14.0), _frame(st, 60, 50, H + 1, Wd, 1000, frame_id=3),
+              _frame(st, 60, 51, H, Wd, 1000, frame_id=4), _frame(st, 60, 50, H, Wd, 700, frame_id=5),
+              _frame(st, 60, 50, H, Wd + 1, 900, frame_id=6)]
+    refl = frames[0].hits.refl
+    for f in frames:
+        f.hits.refl = refl
+    gpol = [W.loss_weights((8601, k), (f.spec.n_range, f.spec.n_azimuth)) for k, f in enumerate(frames)]
+    gfan = [W.loss_weights((8602, k), (f.spec.fan_h, f.spec.fan_w)) for k, f in enumerate(frames)]
+    g_refl, g_par = _plan_backward(frames, refl, gpol, gfan)
+    o_refl, o_par, c_refl, c_par = _oracle(frames, refl, gpol, gfan)
+    assert_grad_cond(g_refl, o_refl, c_refl, what="refl")
+    assert_grad_cond(g_par[0, :5], o_par[0], c_par[0], what="params")
+
+
+@pytest.mark.parametrize("n_bins,side,block_bins", [(1024, 300, 512), (1024, 800, 256), (2048, 400, 1024),
+                                                    (2048, 900, 512), (2048, 1100, 256)])
+def test_operator_rows_per_thread_follow_the_fan_density(n_bins, side, block_bins):
+    """Large batches take several operator rows per thread only where the
+    fan has few pixels per polar bin."""
+    import torch
+    import paper_2503_01074_amd as osm
+    st = W.Stream(8700 + n_bins, side)
+    n = 4
+    spec = W.SonarSpec(r_min=0.5, r_max=12.0, n_range=n_bins, n_azimuth=n_bins, fan_h=side, fan_w=2 * side,
+                       speckle_mode=W.SPECKLE_OFF, alpha=0.09)
+    hits = W.make_hits(st, spec, 2000, n_materials=5)
+    g, h = osm.SonarGeometry.from_spec(spec), osm.DeviceHits.from_host(hits)
+    gpol = W.loss_weights((8701, side), (n_bins, n_bins))
+    gfan = W.loss_weights((8702, side), (side, 2 * side))
+    params = osm.sonar_params([osm.sonar_params_from_spec(spec)])
+    plan = osm.Plan([(g, h)] * n, sonar_params=params, refl=torch.as_tensor(hits.refl).cuda(), backward=True)
+    assert plan.shape()["bwd_block_bins"] == block_bins
+    for o in plan.sonar_out:
+        o["grad_polar"].copy_(torch.as_tensor(gpol))
+        o["grad_fan"].copy_(torch.as_tensor(gfan))
+    plan.forward()
+    plan.backward()
+    torch.cuda.synchronize()
+    g_refl = plan.grad_refl.cpu().numpy().astype(np.float64) / n
+    plan.close()
+    o_refl, _, c_refl, _ = _oracle([W.SonarFrame(spec, hits)], hits.refl, [gpol], [gfan])
+    assert_grad_cond(g_refl, o_refl, c_refl, what="refl")
