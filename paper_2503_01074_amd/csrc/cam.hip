@@ -5,8 +5,8 @@
 //
 // Pure streaming kernels, four consecutive pixels per thread: the byte image
 // moves as dwords (RGB: three per four pixels, RGBA: one dwordx4), planar
-// float images as float4 when the plane size is a multiple of four, depth
-// always as float4.  Decoding is one LDS table lookup per channel; encoding
+// float images and depth as vectors of four.  Decoding is one LDS table lookup
+// per channel; encoding
 // takes a first-guess code from the float's exponent and top mantissa bits
 // and one comparison with the next of 255 LDS thresholds that reproduce the
 // double-precision rounding decision exactly (srgb_tables.hpp), so no power
@@ -135,9 +135,9 @@ __global__ __launch_bounds__(kCamBlock) void k_cam_cond(CamBatch B) {
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
             float *plane = f.J + (size_t)ch * f.hw;
-            if (full && (f.hw & 3u) == 0) {
-                *reinterpret_cast<float4 *>(plane + p) =
-                    make_float4(dec[c[0][ch]], dec[c[1][ch]], dec[c[2][ch]], dec[c[3][ch]]);
+            if (full) {   // (a plane may start at any float: 4-byte aligned vectors)
+                *reinterpret_cast<f32x4_a4_t *>(plane + p) =
+                    f32x4_a4_t{dec[c[0][ch]], dec[c[1][ch]], dec[c[2][ch]], dec[c[3][ch]]};
             } else {
 #pragma unroll
                 for (int k = 0; k < kPix; ++k)
@@ -169,8 +169,8 @@ __global__ __launch_bounds__(kCamBlock) void k_cam_encode(OutBatch B) {
     for (int ch = 0; ch < 3; ++ch) {
         const float *plane = f.I + (size_t)ch * f.hw;
         float x[kPix];
-        if (full && (f.hw & 3u) == 0) {
-            const float4 t = *reinterpret_cast<const float4 *>(plane + p);
+        if (full) {
+            const f32x4_a4_t t = *reinterpret_cast<const f32x4_a4_t *>(plane + p);
             x[0] = t.x, x[1] = t.y, x[2] = t.z, x[3] = t.w;
         } else {
 #pragma unroll

@@ -63,6 +63,19 @@ __device__ __forceinline__ void gstore_stream(gptr<float4> p, float4 v) {
 }
 __device__ __forceinline__ void gstore_stream(gptr<float> p, float v) { __builtin_nontemporal_store(v, p); }
 
+// Four neighbouring floats at any float's address: image planes of a frame
+// whose pixels are not a multiple of four start unaligned to 16 bytes.  The
+// same dwordx4 instructions (global memory takes them at 4-byte alignment), so
+// such frames keep the vector path.
+typedef float f32x4_a4_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 gload_a4(gptr<const float> p) {
+    const f32x4_a4_t v = *(gptr<const f32x4_a4_t>)p;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void gstore_stream_a4(gptr<float> p, float4 v) {
+    __builtin_nontemporal_store(f32x4_a4_t{v.x, v.y, v.z, v.w}, (gptr<f32x4_a4_t>)p);
+}
+
 // --------------------------------------------------------------------------
 // One sonar frame as the kernels see it.  Built on the host from the public
 // descriptor: float inputs promoted exactly to double, derived constants

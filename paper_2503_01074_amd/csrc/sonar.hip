@@ -2205,10 +2205,14 @@ static hipError_t launch_bwd(const Src &src, int n_frames, const SonarGrid &g,
     double *rp = lane_hist ? refl_part : nullptr;
     float *ga = lane_hist ? nullptr : grad_refl;
     if (fuse) {
-        OSIM_DISPATCH_R(g.ret_chunk / kBlock,
-                        OSIM_LAUNCH("k_ret_uw_bwd", (k_ret_uw_bwd<Src, RR>), dim3(g.ret_blocks + uw_blocks),
-                                    dim3(kBlock), lds, st, src, params, refl, n_mat, part, polar_blocks, n_slots, rp,
-                                    ga, g.ret_blocks, *uwb));
+        if constexpr (!std::is_same_v<Src, Table<SonarDev>>) {
+            return hipErrorInvalidValue;   // camera frames come with plans, which launch from tables
+        } else {
+            OSIM_DISPATCH_R(g.ret_chunk / kBlock,
+                            OSIM_LAUNCH("k_ret_uw_bwd", (k_ret_uw_bwd<Src, RR>), dim3(g.ret_blocks + uw_blocks),
+                                        dim3(kBlock), lds, st, src, params, refl, n_mat, part, polar_blocks, n_slots,
+                                        rp, ga, g.ret_blocks, *uwb));
+        }
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     } else {

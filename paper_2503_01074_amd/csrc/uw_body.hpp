@@ -69,8 +69,11 @@ __device__ __forceinline__ float uw_pixel(float J, float d, float bd, float bb, 
     return J * T + bi * S1;
 }
 
-// The full-size camera block body: KIT float4 groups per thread from pixel
-// p0 on, two groups' loads in flight at a time.
+// The full-size camera block body: KIT groups of four pixels per thread from
+// pixel p0 on, two groups' loads in flight at a time.  Planes may start at any
+// float (images whose pixels are not a multiple of four): six frames of 540 x
+// 960, three of them 541 x 961, took 38 us pixel by pixel and take 16 us as
+// vectors, at HBM's rate; their backward 59 and 28 us.
 template <int NT, int KIT>
 __device__ __forceinline__ void uw_fwd_groups(gptr<const float> __restrict__ Jp, gptr<const float> __restrict__ Dp,
                                               gptr<float> __restrict__ Op, long long npix, long long p0, int tx,
@@ -84,7 +87,7 @@ __device__ __forceinline__ void uw_fwd_groups(gptr<const float> __restrict__ Jp,
             const long long p = p0 + ((long long)(i0 + h) * NT + tx) * 4;
             d[h] = gload((gptr<const float4>)(Dp + p));
 #pragma unroll
-            for (int c = 0; c < 3; ++c) J[h][c] = gload((gptr<const float4>)(Jp + c * npix + p));
+            for (int c = 0; c < 3; ++c) J[h][c] = gload_a4(Jp + c * npix + p);
         }
 #pragma unroll
         for (int h = 0; h < KH; ++h) {
@@ -96,7 +99,7 @@ __device__ __forceinline__ void uw_fwd_groups(gptr<const float> __restrict__ Jp,
                 o.y = uw_pixel(J[h][c].y, d[h].y, w.bd[c], w.bb[c], w.bi[c]);
                 o.z = uw_pixel(J[h][c].z, d[h].z, w.bd[c], w.bb[c], w.bi[c]);
                 o.w = uw_pixel(J[h][c].w, d[h].w, w.bd[c], w.bb[c], w.bi[c]);
-                gstore_stream((gptr<float4>)(Op + c * npix + p), o);
+                gstore_stream_a4(Op + c * npix + p, o);
             }
         }
     }
@@ -121,7 +124,7 @@ __device__ __forceinline__ void uw_fwd_block(const Src &src, const oceansim_wate
     const gptr<const float> __restrict__ Jp = f.J;
     const gptr<const float> __restrict__ Dp = f.depth;
     const gptr<float> __restrict__ Op = f.out;
-    if ((npix & 3) == 0 && p0 + (long long)NT * px <= npix) {
+    if (p0 + (long long)NT * px <= npix) {
         switch (px) {
             case 32: uw_fwd_groups<NT, 8>(Jp, Dp, Op, npix, p0, tx, w); break;
             case 16: uw_fwd_groups<NT, 4>(Jp, Dp, Op, npix, p0, tx, w); break;
@@ -130,10 +133,14 @@ __device__ __forceinline__ void uw_fwd_block(const Src &src, const oceansim_wate
         }
         return;
     }
-    // ragged tail (or an image whose size is not a multiple of 4): per pixel
+    // the last, partial block: whole groups, then the image's last pixels
     for (int it = 0; it < px / 4; ++it) {
         const long long p = p0 + ((long long)it * NT + tx) * 4;
-        for (long long q = p; q < p + 4 && q < npix; ++q) {
+        if (p + 4 <= npix) {
+            uw_fwd_groups<NT, 1>(Jp, Dp, Op, npix, p0 + (long long)it * NT * 4, tx, w);
+            continue;
+        }
+        for (long long q = p; q < npix; ++q) {
             const float d = Dp[q];
 #pragma unroll
             for (int c = 0; c < 3; ++c)
@@ -196,8 +203,8 @@ __device__ __forceinline__ void uw_bwd_groups(gptr<const float> __restrict__ Jp,
             d[h] = gload((gptr<const float4>)(Dp + p));
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                J[h][c] = gload((gptr<const float4>)(Jp + c * npix + p));
-                g[h][c] = gload((gptr<const float4>)(Gp + c * npix + p));
+                J[h][c] = gload_a4(Jp + c * npix + p);
+                g[h][c] = gload_a4(Gp + c * npix + p);
             }
         }
 #pragma unroll
@@ -211,7 +218,7 @@ __device__ __forceinline__ void uw_bwd_groups(gptr<const float> __restrict__ Jp,
                 gj.y = uw_pixel_bwd(g[h][c].y, J[h][c].y, d[h].y, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.y);
                 gj.z = uw_pixel_bwd(g[h][c].z, J[h][c].z, d[h].z, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.z);
                 gj.w = uw_pixel_bwd(g[h][c].w, J[h][c].w, d[h].w, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.w);
-                if (IMG && GJ) gstore_stream((gptr<float4>)(GJ + c * npix + p), gj);
+                if (IMG && GJ) gstore_stream_a4(GJ + c * npix + p, gj);
             }
             if (IMG && GD) gstore_stream((gptr<float4>)(GD + p), gdv);
         }
@@ -256,67 +263,63 @@ __device__ __forceinline__ void uw_bwd_block(const Src &src, const oceansim_wate
         const gptr<const float> __restrict__ Gp = f.grad_out;
         const gptr<float> __restrict__ GJ = f.grad_J;
         const gptr<float> __restrict__ GD = f.grad_depth;
-        if ((npix & 3) == 0 && p0 + (long long)NT * px <= npix) {
-            // without image gradients (GJ and GD null) the code is compiled
-            // without them, so their terms are not formed
-            const bool img = GJ || GD;
-            if (!PINNED && n_it == 2) {
-                if (img)
-                    uw_bwd_groups<NT, 2, true>(Jp, Dp, Gp, GJ, GD, npix, p0, tx, w, acc);
-                else
-                    uw_bwd_groups<NT, 2, false>(Jp, Dp, Gp, GJ, GD, npix, p0, tx, w, acc);
-            } else {
-                // one channel at a time: the empty asm statements take the
-                // running sums as operands, so each channel's arithmetic is
-                // done before the next channel's loads are issued
-                auto channels = [&](auto with_img) __attribute__((always_inline)) {
-                    constexpr bool IMG = decltype(with_img)::value;
-#pragma unroll 1
-                    for (int it = 0; it < n_it; ++it) {
-                        const long long p = p0 + ((long long)it * NT + tx) * 4;
-                        const float4 d = gload((gptr<const float4>)(Dp + p));
-                        float4 gdv = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            const float4 J = gload((gptr<const float4>)(Jp + c * npix + p));
-                            const float4 g = gload((gptr<const float4>)(Gp + c * npix + p));
-                            float4 gj;
-                            gj.x = uw_pixel_bwd(g.x, J.x, d.x, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.x);
-                            gj.y = uw_pixel_bwd(g.y, J.y, d.y, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.y);
-                            gj.z = uw_pixel_bwd(g.z, J.z, d.z, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.z);
-                            gj.w = uw_pixel_bwd(g.w, J.w, d.w, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.w);
-                            if (IMG) {
-                                if (GJ) gstore_stream((gptr<float4>)(GJ + c * npix + p), gj);
-                                __asm__ volatile("" : "+v"(acc[c]), "+v"(acc[3 + c]), "+v"(acc[6 + c]), "+v"(gdv.x),
-                                                 "+v"(gdv.y), "+v"(gdv.z), "+v"(gdv.w)::"memory");
-                            } else {
-                                __asm__ volatile("" : "+v"(acc[c]), "+v"(acc[3 + c]), "+v"(acc[6 + c])::"memory");
-                            }
-                        }
-                        if (IMG && GD) gstore_stream((gptr<float4>)(GD + p), gdv);
-                    }
-                };
-                if (img)
-                    channels(std::true_type{});
-                else
-                    channels(std::false_type{});
-            }
+        // without image gradients (GJ and GD null) the code is compiled
+        // without them, so their terms are not formed
+        const bool img = GJ || GD;
+        if (!PINNED && n_it == 2 && p0 + (long long)NT * px <= npix) {
+            if (img)
+                uw_bwd_groups<NT, 2, true>(Jp, Dp, Gp, GJ, GD, npix, p0, tx, w, acc);
+            else
+                uw_bwd_groups<NT, 2, false>(Jp, Dp, Gp, GJ, GD, npix, p0, tx, w, acc);
         } else {
-            // ragged tail (or an image whose size is not a multiple of 4): per pixel
-            for (int it = 0; it < n_it; ++it) {
-                const long long p = p0 + ((long long)it * NT + tx) * 4;
-                for (long long q = p; q < p + 4 && q < npix; ++q) {
-                    const float d = Dp[q];
-                    float gd = 0.0f;
+            // one channel at a time: the empty asm statements take the
+            // running sums as operands, so each channel's arithmetic is
+            // done before the next channel's loads are issued
+            auto channels = [&](auto with_img) __attribute__((always_inline)) {
+                constexpr bool IMG = decltype(with_img)::value;
+#pragma unroll 1
+                for (int it = 0; it < n_it; ++it) {
+                    const long long p = p0 + ((long long)it * NT + tx) * 4;
+                    if (p + 4 > npix) {   // the image's last pixels (in the last block)
+                        for (long long q = p; q < npix; ++q) {
+                            const float d = Dp[q];
+                            float gd = 0.0f;
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) {
+                                const float gj = uw_pixel_bwd(Gp[c * npix + q], Jp[c * npix + q], d, w.bd[c], w.bb[c],
+                                                              w.bi[c], acc, c, gd);
+                                if (IMG && GJ) gstore_stream(GJ + c * npix + q, gj);
+                            }
+                            if (IMG && GD) gstore_stream(GD + q, gd);
+                        }
+                        continue;
+                    }
+                    const float4 d = gload((gptr<const float4>)(Dp + p));
+                    float4 gdv = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
-                        const float gj = uw_pixel_bwd(Gp[c * npix + q], Jp[c * npix + q], d, w.bd[c], w.bb[c],
-                                                      w.bi[c], acc, c, gd);
-                        if (GJ) gstore_stream(GJ + c * npix + q, gj);
+                        const float4 J = gload_a4(Jp + c * npix + p);
+                        const float4 g = gload_a4(Gp + c * npix + p);
+                        float4 gj;
+                        gj.x = uw_pixel_bwd(g.x, J.x, d.x, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.x);
+                        gj.y = uw_pixel_bwd(g.y, J.y, d.y, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.y);
+                        gj.z = uw_pixel_bwd(g.z, J.z, d.z, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.z);
+                        gj.w = uw_pixel_bwd(g.w, J.w, d.w, w.bd[c], w.bb[c], w.bi[c], acc, c, gdv.w);
+                        if (IMG) {
+                            if (GJ) gstore_stream_a4(GJ + c * npix + p, gj);
+                            __asm__ volatile("" : "+v"(acc[c]), "+v"(acc[3 + c]), "+v"(acc[6 + c]), "+v"(gdv.x),
+                                             "+v"(gdv.y), "+v"(gdv.z), "+v"(gdv.w)::"memory");
+                        } else {
+                            __asm__ volatile("" : "+v"(acc[c]), "+v"(acc[3 + c]), "+v"(acc[6 + c])::"memory");
+                        }
                     }
-                    if (GD) gstore_stream(GD + q, gd);
+                    if (IMG && GD) gstore_stream((gptr<float4>)(GD + p), gdv);
                 }
-            }
+            };
+            if (img)
+                channels(std::true_type{});
+            else
+                channels(std::false_type{});
         }
     }
     double accd[9];

@@ -338,6 +338,59 @@ def test_uw_special_cases_and_ragged_batch():
             np.testing.assert_array_equal(g, c.J)   # no water: the clear image, bit for bit
 
 
+@pytest.mark.parametrize("shapes", [[(1, 1)], [(1, 3)], [(1, 5)], [(7, 37)], [(1, 1023)], [(1, 1025)], [(3, 683)],
+                                    [(1, 2047)], [(1, 2050)], [(541, 963)],
+                                    [(1, 4097), (5, 410), (1, 2), (541, 963), (64, 64)]])
+def test_uw_images_of_any_size(shapes):
+    """Pixel counts of every remainder by four (planes that start unaligned
+    to 16 bytes) and around the kernels' blocks of 1024 and 2048 pixels, alone
+    and in one batch: forward, parameter and image gradients; guard pixels
+    around every output stay as they were."""
+    import torch
+    osm = _osm()
+    st = W.Stream(14, sum(h * w for h, w in shapes))
+    cams = [W.make_camera(st, h, w) for h, w in shapes]
+    water = W.make_water(st)
+    gos = [W.loss_weights((14, k), c.J.shape) for k, c in enumerate(cams)]
+    wt = osm.water_params([(water.beta_d, water.beta_b, water.b_inf)])
+    Js = [torch.as_tensor(c.J).cuda() for c in cams]
+    ds = [torch.as_tensor(c.depth).cuda() for c in cams]
+
+    def guarded(shape):   # a view 16-byte aligned inside a larger buffer of a marker value
+        n = int(np.prod(shape))
+        buf = torch.full((n + 64,), 7.0, device="cuda")
+        return buf, buf[32:32 + n].view(shape)
+
+    from paper_2503_01074_amd import _lib, api
+    bufs = [[guarded(c.J.shape), guarded(c.J.shape), guarded(c.depth.shape)] for c in cams]
+    frames = [api._uw_struct(J, d, b[0][1], 0, torch.as_tensor(g).cuda(), b[1][1], b[2][1])
+              for J, d, g, b in zip(Js, ds, gos, bufs)]
+    keep = [torch.as_tensor(g).cuda() for g in gos]
+    for f, g in zip(frames, keep):
+        f.grad_out = g.data_ptr()
+    ws = torch.empty(max(256, _lib.oceansim_uw_workspace_size(frames, True)), dtype=torch.uint8, device="cuda")
+    g_w = torch.empty(1, 9, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    _lib.oceansim_uw_form(frames, wt.data_ptr(), 1, ws.data_ptr(), ws.numel(), s)
+    _lib.oceansim_uw_form_backward(frames, wt.data_ptr(), 1, g_w.data_ptr(), ws.data_ptr(), ws.numel(), s)
+    torch.cuda.synchronize()
+    o_par, c_par = np.zeros(9), np.zeros(9)
+    bd, bb, bi = (x.astype(np.float64) for x in (water.beta_d, water.beta_b, water.b_inf))
+    for k, (c, b) in enumerate(zip(cams, bufs)):
+        for buf, _ in b:
+            assert bool((buf[:32] == 7.0).all()) and bool((buf[-32:] == 7.0).all())
+        assert_image_close(b[0][1].cpu().numpy(), oracle.uw_forward(c.J, c.depth, bd, bb, bi), "uw %d" % k)
+        p, oj, od, cp = oracle.uw_backward(c.J, c.depth, bd, bb, bi, gos[k], with_abs=True)
+        o_par += p
+        c_par += cp
+        assert_image_close(b[1][1].cpu().numpy(), oj, "grad J %d" % k)
+        d = c.depth.astype(np.float64)[None]
+        T, S = np.exp(-bd[:, None, None] * d), np.exp(-bb[:, None, None] * d)
+        cond = (np.abs(gos[k]) * (bd[:, None, None] * np.abs(c.J) * T + bi[:, None, None] * bb[:, None, None] * S)).sum(0)
+        assert np.all(np.abs(b[2][1].cpu().numpy().astype(np.float64) - od) <= 1e-5 * cond + 1e-30), "grad depth %d" % k
+    assert_grad_cond(g_w.cpu().numpy()[0], o_par, c_par, what="water params vs oracle")
+
+
 def test_uw_backward():
     _say("uw_form backward")
     import torch
