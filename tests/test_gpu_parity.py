@@ -169,6 +169,27 @@ def test_dense_collisions():
     check_frame(gpu_forward([f], hits.refl)[0], oracle_forward(f, hits.refl), "dense")
 
 
+@pytest.mark.parametrize("n_hot", [1, 2, 7, 64])
+@pytest.mark.parametrize("n_az", [15, 129])
+def test_returns_piled_up_in_few_bins(n_hot, n_az):
+    """Returns on the x axis at n_hot ranges, all facing the sensor without
+    attenuation: intensities are the reflectivities 1 and 1/2 exactly, so the
+    sums of lanes that change the same histogram word at once are exact."""
+    spec = W.SonarSpec(r_min=1.0, r_max=65.0, n_range=64, n_azimuth=n_az, speckle_mode=W.SPECKLE_OFF, alpha=0.0)
+    n = 40001
+    st = W.Stream(15, n_hot)
+    row = st.integers(0, n_hot - 1, n)
+    x = (1.5 + row).astype(np.float32)
+    z = np.zeros(n, np.float32)
+    mat = st.integers(0, 1, n).astype(np.int32)
+    hits = W.SonarHits(x=x, y=z, z=z.copy(), nx=np.full(n, -1, np.float32), ny=z.copy(), nz=z.copy(), mat=mat,
+                       refl=np.array([1.0, 0.5], np.float32))
+    want = np.zeros((64, n_az))
+    np.add.at(want, (row, n_az // 2), hits.refl[mat])
+    got = gpu_forward([W.SonarFrame(spec, hits)], hits.refl, fan=False)[0]
+    np.testing.assert_array_equal(got["polar"], want.astype(np.float32))
+
+
 def test_batched_equals_plain_and_oracle():
     _say("batched uneven frames")
     frames = W.sonar_c3(n_frames=6)
