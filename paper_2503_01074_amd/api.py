@@ -23,7 +23,14 @@ def _ptr(t: Optional[torch.Tensor]) -> int:
     return 0 if t is None else t.data_ptr()
 
 
+# the current stream's handle without a Stream object around it (1.8 us)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
+    index = getattr(device, "index", None)
+    if _raw_stream is not None and index is not None:
+        return _raw_stream(index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
@@ -131,6 +138,26 @@ def _sonar_struct(g: SonarGeometry, h: DeviceHits, polar=None, fan=None, bins=No
     return s
 
 
+# Hot paths fill whole frame arrays with one struct.pack_into per frame (0.4 us
+# against 1.7 us field by field).  Values it refuses (out of range, or of
+# another type) go through the field-by-field builders, which convert or refuse
+# them as ever.
+def _pack_sonar(arr, i: int, g: SonarGeometry, h: DeviceHits, polar=None, fan=None, bins=None, grad_polar=None,
+                grad_fan=None, stencil=None, saved_p=None) -> None:
+    try:
+        _lib.PACK_SONAR.pack_into(
+            arr, i * _lib.PACK_SONAR.size, h.x.data_ptr(), h.y.data_ptr(), h.z.data_ptr(), h.nx.data_ptr(),
+            h.ny.data_ptr(), h.nz.data_ptr(), h.mat.data_ptr(), h.x.numel(), g.r_min, g.r_max, g.fov_az, g.fov_el,
+            g.path_factor, g.n_range, g.n_azimuth, g.fan_h, g.fan_w, g.speckle_mode, g.gamma_k, g.param_row,
+            g.seed_lo & 0xFFFFFFFF, g.seed_hi & 0xFFFFFFFF, g.frame_id & 0xFFFFFFFF,
+            0 if polar is None else polar.data_ptr(), 0 if fan is None else fan.data_ptr(),
+            0 if bins is None else bins.data_ptr(), 0 if grad_polar is None else grad_polar.data_ptr(),
+            0 if grad_fan is None else grad_fan.data_ptr(), 0 if stencil is None else stencil.data_ptr(),
+            int(g.range_norm), 0 if saved_p is None else saved_p.data_ptr())
+    except _lib.PACK_ERRORS:
+        arr[i] = _sonar_struct(g, h, polar, fan, bins, grad_polar, grad_fan, stencil, saved_p)
+
+
 def fan_stencil_buffer(g: SonarGeometry, device) -> Optional[torch.Tensor]:
     """Device buffer for the saved fan stencils of a frame (None without a fan)."""
     n = _lib.oceansim_fan_stencil_size(g.fan_h, g.fan_w)
@@ -146,12 +173,15 @@ def render_sonar(geoms: Sequence[SonarGeometry], hits: Sequence[DeviceHits], par
     fan stencils, to hand to render_sonar_backward.  A range-normalised frame
     also returns "saved_p", the binned sums its backward needs."""
     device = params.device
-    outs, structs = [], []
-    for g, h in zip(geoms, hits):
+    frames = list(zip(geoms, hits))
+    structs = (SonarFrame * len(frames))()
+    outs = []
+    for i, (g, h) in enumerate(frames):
         o = {}
-        if polar or not (fan and g.fan_h > 0):
+        has_fan = fan and g.fan_h > 0
+        if polar or not has_fan:
             o["polar"] = torch.empty(g.n_range, g.n_azimuth, dtype=torch.float32, device=device)
-        if fan and g.fan_h > 0 and g.fan_w > 0:
+        if has_fan and g.fan_w > 0:
             o["fan"] = torch.empty(g.fan_h, g.fan_w, dtype=torch.float32, device=device)
             if save_stencil:
                 o["stencil"] = fan_stencil_buffer(g, device)
@@ -160,8 +190,8 @@ def render_sonar(geoms: Sequence[SonarGeometry], hits: Sequence[DeviceHits], par
         if g.range_norm:
             o["saved_p"] = torch.empty(g.n_range, g.n_azimuth, dtype=torch.float32, device=device)
         outs.append(o)
-        structs.append(_sonar_struct(g, h, o.get("polar"), o.get("fan"), o.get("bins"),
-                                     stencil=o.get("stencil"), saved_p=o.get("saved_p")))
+        _pack_sonar(structs, i, g, h, o.get("polar"), o.get("fan"), o.get("bins"), stencil=o.get("stencil"),
+                    saved_p=o.get("saved_p"))
     n_mat = int(refl.numel())
     need = _lib.oceansim_sonar_workspace_size(structs, n_mat, False)
     ws = workspace if workspace is not None and workspace.numel() >= need else _workspace(need, device)
@@ -184,8 +214,10 @@ def render_sonar_backward(geoms: Sequence[SonarGeometry], hits: Sequence[DeviceH
     device = params.device
     stencils = stencils or [None] * len(geoms)
     saved_p = saved_p or [None] * len(geoms)
-    structs = [_sonar_struct(g, h, grad_polar=gp, grad_fan=gf, stencil=sv, saved_p=sp)
-               for g, h, gp, gf, sv, sp in zip(geoms, hits, grad_polar, grad_fan, stencils, saved_p)]
+    frames = list(zip(geoms, hits, grad_polar, grad_fan, stencils, saved_p))
+    structs = (SonarFrame * len(frames))()
+    for i, (g, h, gp, gf, sv, sp) in enumerate(frames):
+        _pack_sonar(structs, i, g, h, grad_polar=gp, grad_fan=gf, stencil=sv, saved_p=sp)
     n_mat = int(refl.numel())
     need = _lib.oceansim_sonar_workspace_size(structs, n_mat, True)
     ws = workspace if workspace is not None and workspace.numel() >= need else _workspace(need, device)
@@ -205,12 +237,27 @@ def _uw_struct(J, depth, out=None, row=0, grad_out=None, grad_J=None, grad_depth
     return s
 
 
+def _pack_uw(arr, i: int, J, depth, out=None, row=0, grad_out=None, grad_J=None, grad_depth=None) -> None:
+    try:
+        shape = depth.shape
+        _lib.PACK_UW.pack_into(arr, i * _lib.PACK_UW.size, J.data_ptr(), depth.data_ptr(),
+                               0 if out is None else out.data_ptr(), shape[-2], shape[-1], row,
+                               0 if grad_out is None else grad_out.data_ptr(),
+                               0 if grad_J is None else grad_J.data_ptr(),
+                               0 if grad_depth is None else grad_depth.data_ptr())
+    except _lib.PACK_ERRORS:
+        arr[i] = _uw_struct(J, depth, out, row, grad_out, grad_J, grad_depth)
+
+
 def uw_form(Js: Sequence[torch.Tensor], depths: Sequence[torch.Tensor], water: torch.Tensor,
             rows: Optional[Sequence[int]] = None) -> List[torch.Tensor]:
     """Eq. (1) on planar [3, H, W] images with depths [H, W] (one launch)."""
     rows = rows or [0] * len(Js)
     outs = [torch.empty_like(J) for J in Js]
-    structs = [_uw_struct(J, d, o, r) for J, d, o, r in zip(Js, depths, outs, rows)]
+    frames = list(zip(Js, depths, outs, rows))
+    structs = (UwFrame * len(frames))()
+    for i, (J, d, o, r) in enumerate(frames):
+        _pack_uw(structs, i, J, d, o, r)
     need = _lib.oceansim_uw_workspace_size(structs, False)
     ws = _workspace(need, water.device) if len(Js) > 1 else None
     _lib.oceansim_uw_form(structs, _ptr(water), int(water.shape[0]), _ptr(ws), 0 if ws is None else ws.numel(),
@@ -220,17 +267,24 @@ def uw_form(Js: Sequence[torch.Tensor], depths: Sequence[torch.Tensor], water: t
 
 def uw_form_backward(Js, depths, water: torch.Tensor, grad_outs, rows=None, want_image_grads=True):
     """(grad_water [rows, 9], grad_J list, grad_depth list)."""
+    g_w = torch.empty(water.shape[0], WATER_GRAD_WIDTH, dtype=torch.float32, device=water.device)
+    return (g_w, *_uw_backward(Js, depths, water, grad_outs, rows, want_image_grads, g_w))
+
+
+def _uw_backward(Js, depths, water, grad_outs, rows, want_image_grads, g_w):
+    """uw_form_backward into g_w: water.shape[0] rows of WATER_GRAD_WIDTH floats, back to back."""
     rows = rows or [0] * len(Js)
     gJ = [torch.empty_like(J) if want_image_grads else None for J in Js]
     gd = [torch.empty_like(d) if want_image_grads else None for d in depths]
-    structs = [_uw_struct(J, d, None, r, go, a, b)
-               for J, d, r, go, a, b in zip(Js, depths, rows, grad_outs, gJ, gd)]
+    frames = list(zip(Js, depths, rows, grad_outs, gJ, gd))
+    structs = (UwFrame * len(frames))()
+    for i, (J, d, r, go, a, b) in enumerate(frames):
+        _pack_uw(structs, i, J, d, None, r, go, a, b)
     need = _lib.oceansim_uw_workspace_size(structs, True)
     ws = _workspace(need, water.device)
-    g_w = torch.empty(water.shape[0], WATER_GRAD_WIDTH, dtype=torch.float32, device=water.device)
     _lib.oceansim_uw_form_backward(structs, _ptr(water), int(water.shape[0]), _ptr(g_w), _ptr(ws), ws.numel(),
                                    _stream(water.device))
-    return g_w, gJ, gd
+    return gJ, gd
 
 
 # --------------------------------------------------------------------------- #
@@ -247,12 +301,26 @@ def _cam_struct(H, W, intr, srgb=None, zdepth=None, J=None, rng=None, grad_range
     return s
 
 
+def _pack_cam(arr, i: int, H, W, intr, srgb=None, zdepth=None, J=None, rng=None, grad_range=None,
+              grad_z=None) -> None:
+    intr = tuple(intr)
+    try:
+        fx, fy, cx, cy = intr
+        _lib.PACK_CAM.pack_into(
+            arr, i * _lib.PACK_CAM.size, 0 if srgb is None else srgb.data_ptr(),
+            0 if zdepth is None else zdepth.data_ptr(), 0 if J is None else J.data_ptr(),
+            0 if rng is None else rng.data_ptr(), 0 if grad_range is None else grad_range.data_ptr(),
+            0 if grad_z is None else grad_z.data_ptr(), H, W, 3 if srgb is None else srgb.shape[-1], fx, fy, cx, cy)
+    except (*_lib.PACK_ERRORS, ValueError):
+        arr[i] = _cam_struct(H, W, intr, srgb, zdepth, J, rng, grad_range, grad_z)
+
+
 def cam_condition(srgbs: Sequence[Optional[torch.Tensor]], zdepths: Sequence[Optional[torch.Tensor]],
                   intrinsics: Sequence[Sequence[float]]):
     """Frames of uint8 sRGB [H, W, 3 or 4] and/or z-depth [H, W] (either may be
     None) -> (list of linear planar J [3, H, W] or None, list of range [H, W] or
     None), one launch per 16 frames.  intrinsics: (fx, fy, cx, cy) per frame."""
-    Js, rngs, structs = [], [], []
+    Js, rngs, work = [], [], []
     for srgb, z, intr in zip(srgbs, zdepths, intrinsics):
         ref = srgb if srgb is not None else z
         if ref is None:             # nothing to condition in this frame
@@ -264,8 +332,11 @@ def cam_condition(srgbs: Sequence[Optional[torch.Tensor]], zdepths: Sequence[Opt
         r = torch.empty_like(z) if z is not None else None
         Js.append(J)
         rngs.append(r)
-        structs.append(_cam_struct(H, W, intr, srgb, z, J, r))
-    if structs:
+        work.append((H, W, intr, srgb, z, J, r))
+    if work:
+        structs = (CamFrame * len(work))()
+        for i, f in enumerate(work):
+            _pack_cam(structs, i, *f)
         dev = next(t for t in list(srgbs) + list(zdepths) if t is not None).device   # noqa: E501
         _lib.oceansim_cam_condition(structs, _stream(dev))
     return Js, rngs
@@ -274,24 +345,30 @@ def cam_condition(srgbs: Sequence[Optional[torch.Tensor]], zdepths: Sequence[Opt
 def cam_condition_backward(grad_ranges: Sequence[torch.Tensor], intrinsics: Sequence[Sequence[float]]):
     """dL/d(range) [H, W] per frame -> dL/d(z-depth) [H, W] per frame."""
     gz = [torch.empty_like(g) for g in grad_ranges]
-    structs = [_cam_struct(g.shape[0], g.shape[1], intr, grad_range=g, grad_z=o)
-               for g, o, intr in zip(grad_ranges, gz, intrinsics)]
-    if structs:
+    work = list(zip(grad_ranges, gz, intrinsics))
+    if work:
+        structs = (CamFrame * len(work))()
+        for i, (g, o, intr) in enumerate(work):
+            _pack_cam(structs, i, g.shape[0], g.shape[1], intr, grad_range=g, grad_z=o)
         _lib.oceansim_cam_condition_backward(structs, _stream(grad_ranges[0].device))
     return gz
 
 
 def cam_encode(images: Sequence[torch.Tensor], channels_out: int = 3) -> List[torch.Tensor]:
     """Planar linear [3, H, W] float images -> uint8 sRGB [H, W, channels_out]."""
-    outs, structs = [], []
-    for I in images:
+    outs = []
+    structs = (CamOutFrame * len(images))()
+    for i, I in enumerate(images):
         H, W = int(I.shape[-2]), int(I.shape[-1])
         o = torch.empty(H, W, channels_out, dtype=torch.uint8, device=I.device)
-        s = CamOutFrame()
-        s.I, s.srgb_out, s.H, s.W, s.channels_out = _ptr(I), _ptr(o), H, W, channels_out
         outs.append(o)
-        structs.append(s)
-    if structs:
+        try:
+            _lib.PACK_CAM_OUT.pack_into(structs, i * _lib.PACK_CAM_OUT.size, I.data_ptr(), o.data_ptr(), H, W,
+                                        channels_out)
+        except _lib.PACK_ERRORS:
+            s = structs[i]
+            s.I, s.srgb_out, s.H, s.W, s.channels_out = _ptr(I), _ptr(o), H, W, channels_out
+    if outs:
         _lib.oceansim_cam_encode(structs, _stream(images[0].device))
     return outs
 
@@ -397,13 +474,20 @@ def raycast(scene: Scene, poses: Sequence, n_beams: int, n_rays: int, fov_az: fl
             res.append(DeviceHits(f32(), f32(), f32(), f32(), f32(), f32(),
                                   torch.empty(n, dtype=torch.int32, device=device)))
         h = res[i]
-        fr = frames[i]
-        fr.pos[:] = [float(v) for v in np.asarray(pos, dtype=np.float64).reshape(3)]
-        fr.rot[:] = [float(v) for v in np.asarray(rot, dtype=np.float64).reshape(9)]
-        fr.n_beams, fr.n_rays = int(n_beams), int(n_rays)
-        fr.fov_az, fr.fov_el, fr.t_max = float(fov_az), float(fov_el), float(t_max)
-        for k in ("x", "y", "z", "nx", "ny", "nz", "mat"):
-            setattr(fr, k, _ptr(getattr(h, k)))
+        p = np.asarray(pos, dtype=np.float64).reshape(3).tolist()
+        r = np.asarray(rot, dtype=np.float64).reshape(9).tolist()
+        try:
+            _lib.PACK_RAY.pack_into(frames, i * _lib.PACK_RAY.size, *p, *r, int(n_beams), int(n_rays), float(fov_az),
+                                    float(fov_el), float(t_max), h.x.data_ptr(), h.y.data_ptr(), h.z.data_ptr(),
+                                    h.nx.data_ptr(), h.ny.data_ptr(), h.nz.data_ptr(), h.mat.data_ptr())
+        except _lib.PACK_ERRORS:
+            fr = frames[i]
+            fr.pos[:] = p
+            fr.rot[:] = r
+            fr.n_beams, fr.n_rays = int(n_beams), int(n_rays)
+            fr.fov_az, fr.fov_el, fr.t_max = float(fov_az), float(fov_el), float(t_max)
+            for k in ("x", "y", "z", "nx", "ny", "nz", "mat"):
+                setattr(fr, k, _ptr(getattr(h, k)))
     dev = res[0].x.device if res else torch.device(device)
     _lib.oceansim_raycast(scene.handle, frames, len(poses), _stream(dev))
     return res
@@ -559,9 +643,14 @@ class UwForm(torch.autograd.Function):
         water, *images = ctx.saved_tensors
         Js, ds = images[0::2], images[1::2]
         gos = [torch.zeros_like(J) if g is None else g.contiguous() for g, J in zip(grads, Js)]
-        g_w, gJ, gd = uw_form_backward(Js, ds, water, gos, ctx.rows, want_image_grads=True)
         gw = torch.zeros_like(water)
-        gw[:, :WATER_GRAD_WIDTH] = g_w
+        if water.dtype == torch.float32 and water.shape[0] == 1 and water.shape[1] >= WATER_GRAD_WIDTH and \
+                gw.is_contiguous():
+            # one row: its gradient is the first WATER_GRAD_WIDTH floats of gw
+            gJ, gd = _uw_backward(Js, ds, water, gos, ctx.rows, True, gw)
+        else:
+            g_w, gJ, gd = uw_form_backward(Js, ds, water, gos, ctx.rows, want_image_grads=True)
+            gw[:, :WATER_GRAD_WIDTH] = g_w
         img_grads = []
         for a, b in zip(gJ, gd):
             img_grads += [a, b]
