@@ -229,6 +229,20 @@ __host__ __device__ __forceinline__ FusedSlot fused_slot(long long x, int n_tile
     return c_upto > c_before ? FusedSlot{true, c_before} : FusedSlot{false, (int)(x - c_before)};
 }
 
+// The same for short workgroups: c(x) = floor(x m / 2^32) with m = ceil(C 2^32 /
+// N) in place of floor(x C / N), one high product instead of two 64-bit
+// divisions.  c(0) = 0, c(N) = C for N < 2^32, and c steps by 0 or 1, so again
+// every workgroup of both kinds is taken exactly once.  (n_tile > 0.)
+__host__ __device__ __forceinline__ unsigned fused_ratio(int n_tile, int n_cam) {
+    const unsigned long long n = (unsigned long long)n_tile + (unsigned)n_cam;
+    return (unsigned)((((unsigned long long)(unsigned)n_cam << 32) + n - 1) / n);
+}
+__host__ __device__ __forceinline__ FusedSlot fused_slot_by_ratio(unsigned x, unsigned m) {
+    const int c_before = (int)(((unsigned long long)x * m) >> 32);
+    const int c_upto = (int)((((unsigned long long)x + 1) * m) >> 32);
+    return c_upto > c_before ? FusedSlot{true, c_before} : FusedSlot{false, (int)x - c_before};
+}
+
 // Frame sources: a single frame passed by value in the kernel arguments, or a
 // device-resident table (batched calls and plans).  Workgroups find their
 // frame by a uniform binary search over the per-frame first-block indices.

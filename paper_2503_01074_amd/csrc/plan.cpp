@@ -47,7 +47,7 @@ struct oceansim_plan {
     char *ws_sf = nullptr, *ws_sb = nullptr, *ws_uf = nullptr, *ws_ub = nullptr;
     hipStream_t cap = nullptr;   // capture stream (default priority)
     // with both kinds of frames the camera frames ride along in the forward
-    // binning launch of the sonar frames
+    // launches of the sonar frames
     bool fused = false;
     // the backward runs from the forward's material pairs (k_pair_bwd)
     bool pair = false;

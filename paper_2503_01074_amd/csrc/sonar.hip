@@ -13,7 +13,9 @@
 //           bin and streams the tile out row-major.
 //   k_fan   one thread per mirror pair of fan pixels: FP64 polar coordinates,
 //           bilinear interpolation of the polar image.
-//   k_bin_uw    (plans with camera frames) k_bin plus the camera forward.
+//   k_bin_uw    (plans with camera frames) k_bin plus the camera forward, or
+//               the part of it that does not ride in k_fan_uw.
+//   k_fan_uw    (plans with larger camera frames) k_fan plus that part.
 //   k_tile_uw   (plans with camera frames and wide tiles) k_tile plus the
 //               camera forward, workgroups of both kinds interleaved.
 // Backward, per frame:
@@ -186,8 +188,9 @@ __global__ __launch_bounds__(NT) void k_bin(Src src, const oceansim_sonar_params
 }
 
 // The binning chunks of the sonar frames and, in the same launch, the camera
-// forward of a plan (workgroups n_bin_blocks and up): the chunks are few and
-// latency-bound, so the camera's HBM stream fills the rest of the chip.
+// forward of a plan, or its first blocks (workgroups n_bin_blocks and up; the
+// rest ride in k_fan_uw, see cam_in_fan): the chunks are few and latency-bound,
+// so the camera's HBM stream fills the rest of the chip.
 template <class Src, int R>
 __global__ __launch_bounds__(kBlock) void k_bin_uw(Src src, const oceansim_sonar_params *params,
                                                    const float *refl, int n_mat, int n_bin_blocks,
@@ -593,10 +596,10 @@ __device__ __forceinline__ float2 polar_pair_at(gptr<const float> base, int idx)
 
 // IMAGE = false: the stencil records alone (geometry only; the polar image is
 // not read and the fan is not written).
-template <class Src, bool IMAGE = true>
-__global__ __launch_bounds__(kBlock) void k_fan(Src src) {
+template <class Src, bool IMAGE>
+__device__ __forceinline__ void fan_block(const Src &src, int bid) {
     int local;
-    const int fi = src.locate(xcd_grouped_id<16>(blockIdx.x, gridDim.x), KFAN, local);
+    const int fi = src.locate(bid, KFAN, local);
     const SonarDev f = src.frame(fi);
     // a workgroup covers kFanTileU pixel pairs x kFanTileV rows; each wave an 8 x 8 patch
     // of pairs per load instruction (rows 8 apart across a thread's kFanRows),
@@ -731,6 +734,23 @@ __global__ __launch_bounds__(kBlock) void k_fan(Src src) {
         row += row_step;
         if (rec) rec += rec_step;
     }
+}
+
+template <class Src, bool IMAGE = true>
+__global__ __launch_bounds__(kBlock) void k_fan(Src src) {
+    fan_block<Src, IMAGE>(src, xcd_grouped_id<16>(blockIdx.x, gridDim.x));
+}
+
+// The fan and blocks [cam0, cam0 + n) of a plan's camera forward in one launch,
+// interleaved (ratio: fused_ratio of the two counts; cam_in_fan says how many):
+// the fan waits on its gathers and its arithmetic, the camera on HBM.
+__global__ __launch_bounds__(kBlock) void k_fan_uw(Table<SonarDev> src, unsigned ratio, Table<UwDev> usrc,
+                                                   const oceansim_water_params *wparams, int cam0) {
+    const FusedSlot slot = fused_slot_by_ratio((unsigned)xcd_grouped_id<16>(blockIdx.x, gridDim.x), ratio);
+    if (slot.cam)
+        uw_fwd_block<Table<UwDev>, kBlock>(usrc, wparams, cam0 + slot.index, threadIdx.x);
+    else
+        fan_block<Table<SonarDev>, true>(src, slot.index);
 }
 
 // ---------------------------------------------------------------------------
@@ -2027,6 +2047,25 @@ __global__ __launch_bounds__(kBlock) void k_reduce_sonar(SonarReduce a) {
         default: return hipErrorInvalidValue;          \
     }
 
+// Camera blocks of a plan's forward that ride in the fan launch rather than in
+// the binning launch.  Both launches wait on latency beside the camera's
+// stream, so the camera is split over the two, 5/8 of it in the fan's, which
+// has more workgroups in flight.  A plan forward with all of it in the binning
+// launch -> split, in us (sonar frames of R x C bins + as many images):
+//   1 x 1024 x 1024 + 1080p 31.1 -> 28.8    4 of them 89 -> 82    8: 165 -> 148
+//   4 x 512 x 512 + 540p    32.6 -> 29.5    12 of them 70 -> 68
+// A camera of less than 1024 blocks (4 a CU) is through while the first chunks
+// are still binned, and in the fan's launch would only lengthen it:
+//   1 x 512 x 256 + 540p (507 blocks) 17.7 -> 18.1
+//   1 x 512 x 512 + 720p (900 blocks) 18.9 -> 19.1
+// No more blocks than there are fan workgroups to ride with, and the sum within
+// a launch's 2^32 threads.
+static int cam_in_fan(int cam_blocks, int fan_blocks) {
+    if (cam_blocks < 1024 || fan_blocks >= (1 << 23)) return 0;
+    const long long share = (long long)cam_blocks * 5 / 8;
+    return (int)(share < fan_blocks ? share : fan_blocks);
+}
+
 template <class Src>
 static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_sonar_params *params,
                              const float *refl, int n_mat, hipStream_t st, const UwCompanion *uw) {
@@ -2036,6 +2075,10 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
     // frames then run in a launch of their own
     const bool wide = g.chunk > 4096;
     const bool with_uw = uw && uw->blocks > 0;
+    int cam_fan = 0;
+    if constexpr (std::is_same_v<Src, Table<SonarDev>>)
+        if (with_uw && !wide) cam_fan = cam_in_fan(uw->blocks, g.fan_blocks);
+    const int cam_bin = with_uw ? uw->blocks - cam_fan : 0;
     if (g.bin_blocks > 0 || (with_uw && !wide)) {
         const size_t lds = (size_t)((g.max_tiles + 1 + 3) & ~3) * 4 + (size_t)g.chunk * 8;
         if (wide) {
@@ -2044,7 +2087,7 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
                         src, params, refl, n_mat);
         } else if (with_uw) {
             OSIM_DISPATCH_R(g.chunk / kBlock,
-                            OSIM_LAUNCH("k_bin_uw", (k_bin_uw<Src, RR>), dim3(g.bin_blocks + uw->blocks),
+                            OSIM_LAUNCH("k_bin_uw", (k_bin_uw<Src, RR>), dim3(g.bin_blocks + cam_bin),
                                         dim3(kBlock), lds, st, src, params, refl, n_mat, g.bin_blocks,
                                         Table<UwDev>{uw->table, uw->n}, uw->params));
         } else {
@@ -2089,7 +2132,12 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (g.fan_blocks > 0) {
+    if (cam_fan > 0) {
+        if constexpr (std::is_same_v<Src, Table<SonarDev>>)
+            OSIM_LAUNCH("k_fan_uw", k_fan_uw, dim3(g.fan_blocks + cam_fan), dim3(kBlock), 0, st, src,
+                        fused_ratio(g.fan_blocks, cam_fan), Table<UwDev>{uw->table, uw->n}, uw->params, cam_bin);
+        e = hipGetLastError();
+    } else if (g.fan_blocks > 0) {
         OSIM_LAUNCH("k_fan", (k_fan<Src>), dim3(g.fan_blocks), dim3(kBlock), 0, st, src);
         e = hipGetLastError();
     }

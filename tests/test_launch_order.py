@@ -189,3 +189,55 @@ def test_segment_map_finds_every_index(tmp_path):
     assert r.returncode == 0, r.stderr[-3000:]
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
+
+
+RATIO_PROGRAM = r"""
+#include "device.hpp"
+#include <cstdio>
+#include <vector>
+
+using namespace osim;
+
+// fan and camera blocks of the plan's forward: each taken once, the camera's in
+// order and evenly spread
+static int check(int n_tile, int n_cam) {
+    const unsigned m = fused_ratio(n_tile, n_cam);
+    std::vector<char> tiles(n_tile, 0), cams(n_cam, 0);
+    for (unsigned x = 0; x < (unsigned)(n_tile + n_cam); ++x) {
+        const FusedSlot s = fused_slot_by_ratio(x, m);
+        if (s.index < 0 || s.index >= (s.cam ? n_cam : n_tile)) return 1;
+        if ((s.cam ? cams : tiles)[s.index]++) return 2;
+        const FusedSlot w = fused_slot(x, n_tile, n_cam);
+        const int before = s.cam ? s.index : (int)x - s.index, want = w.cam ? w.index : (int)x - w.index;
+        if (before < want || before > want + 1) return 3;
+    }
+    return 0;
+}
+
+int main() {
+    for (int t = 1; t <= 70; ++t)
+        for (int c = 1; c <= 70; ++c)
+            if (int e = check(t, c)) { printf("t=%d c=%d error %d\n", t, c, e); return 1; }
+    const int tiles[] = {1, 2, 3, 640, 1023, 2025, 65537, 1000003, (1 << 23) - 1};
+    const int cams[] = {1, 2, 3, 640, 1265, 2025, 65536, 999983, 1 << 23};
+    for (int t : tiles)
+        for (int c : cams)
+            if (int e = check(t, c)) { printf("t=%d c=%d error %d\n", t, c, e); return 1; }
+    printf("ok\n");
+    return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="hipcc not available")
+def test_interleaving_by_ratio_is_a_bijection(tmp_path):
+    src = tmp_path / "ratio.hip"
+    exe = tmp_path / "ratio"
+    src.write_text(RATIO_PROGRAM)
+    hipcc = HIPCC if os.path.exists(HIPCC) else shutil.which("hipcc")
+    r = subprocess.run([hipcc, "-x", "hip", "--cuda-host-only", "-std=c++17", "-O2", "-I", CSRC,
+                        "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
