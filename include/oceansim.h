@@ -500,15 +500,15 @@ enum {
  * grad_water_params_dev [n_water_rows][9] (each may be NULL when there are no
  * frames of that kind).  The fan of a frame is a fixed linear map of its
  * polar image; for frames with a fan and a fan gradient a backward plan
- * builds the transpose of that map once, at creation (for each polar bin,
- * the fan pixels that read it and their bilinear weights, from the same
- * stencils the fan kernel computes: one int per bin plus 8 bytes per
- * pixel-bin pair, on the order of 40 bytes per fan pixel), and its backward
+ * builds the transpose of that map once, at creation (for each pair of
+ * neighbouring bins of a range row, the fan pixels that read it and their
+ * bilinear weights, from the same stencils the fan kernel computes: one int
+ * per bin plus 12 bytes per pixel and range row, on the order of 30 bytes per fan pixel), and its backward
  * gathers each bin's fan gradient through it.  With an even fan width (at
  * most 65535 x 65535 pixels) the two halves of the fan are exact mirror
  * images, and the operator holds the bins of the first ceil(n_azimuth / 2)
  * columns only: each also yields its mirror bin from the mirrored pixels
- * (about 20 bytes per fan pixel).  The plan's forward saves no
+ * (about 15 bytes per fan pixel).  The plan's forward saves no
  * stencils (a caller's own fan_stencil buffer is still written).  The
  * forward is the image formation of oceansim_sonar_render (Sec. III-A.2,
  * Eq. 2-6, and the fan) and oceansim_uw_form (Sec. III-A.1, Eq. 1); the
@@ -547,8 +547,9 @@ int oceansim_plan_forward(oceansim_plan *plan, void *stream);
 int oceansim_plan_backward(oceansim_plan *plan, void *stream);
 
 /* Launch shapes in use: {forward tile bins, returns per chunk, operator rows
- * per backward workgroup (a row is a polar bin, or a bin and its mirror bin;
- * 0 without a sonar backward), graphs in use (0/1)}. */
+ * per thread of a backward workgroup times its 256 threads (a row is a polar
+ * bin, or a bin and its mirror bin; 0 without a sonar backward), graphs in
+ * use (0/1)}. */
 int oceansim_plan_shape(const oceansim_plan *plan, int32_t shape[4]);
 
 /* Frees the plan's device memory and graphs (after synchronising the

@@ -212,12 +212,13 @@ int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_row
     // the workgroups fit the chip a few times over; two or four for large
     // batches, where the per-workgroup costs (frame lookup, pointer loads,
     // partial sums) add up, but only while rows are short: a thread sums its
-    // rows' entries one after the other, and a row has about four entries per
+    // rows' entries one after the other, and a row has about two entries per
     // fan pixel per bin.  Measured at 4 frames (1, 2, 4 rows per thread, us;
-    // mirrored operators): 1024^2 bins with 0.17 pixels a bin 33, 30, 31, with
-    // 0.69 34, 37, 52, with 3.7 87, 132, 467; 2048^2 with 0.04 108, 94, 91, with
-    // 0.39 121, 113, 126, with 0.93 149, 149, 202.  Plain operators (half the
-    // gathers a row): 1024^2 with 1.5 52, 51, 78, with 3.7 110, 115, 258.
+    // mirrored operators): 1024^2 bins with 0.17 pixels a bin 29, 26, 29, with
+    // 0.69 30, 31, 45, with 3.7 53, 119, 475; 2048^2 with 0.04 90, 74, 81, with
+    // 0.39 97, 86, 101, with 0.93 120, 116, 169.  Plain operators (half the
+    // gathers a row): 1024^2 with 1.5 50, 50, 101, with 3.7 77, 121, 429; 2048^2
+    // with 0.04 137, 92, 75.
     int fant_bpt = total_nb >= (16LL << 20) ? 4 : (total_nb >= (2LL << 20) ? 2 : 1);
     if (backward && fant_bpt > 1) {
         double px = 0.0;
@@ -271,7 +272,7 @@ int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_row
         // the pair backward reads the polar gradient of frames without a
         // transposed fan operator directly: operator rows for the others only
         const bool fant_rows = backward && (!pair_mode || fan_operator_layout(fr) != 0);
-        d.n_fant_blocks = fant_rows ? (int)((op_rows + kBlock * fant_bpt - 1) / (kBlock * fant_bpt)) : 0;
+        d.n_fant_blocks = fant_rows ? (int)((op_rows + kFantRows * fant_bpt - 1) / (kFantRows * fant_bpt)) : 0;
         fant_blocks += d.n_fant_blocks;
         bin_blocks += d.n_chunks;
         tile_blocks += d.n_tiles;

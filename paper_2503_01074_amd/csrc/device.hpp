@@ -81,6 +81,13 @@ __device__ __forceinline__ void gstore_stream_a4(gptr<float> p, float4 v) {
 // descriptor: float inputs promoted exactly to double, derived constants
 // computed once in double.
 // --------------------------------------------------------------------------
+// Entry of a transposed fan operator: a fan pixel and its bilinear weights on
+// the two bins of its cell.
+struct FanEntry {
+    unsigned pixel;
+    float w0, w1;
+};
+
 struct SonarDev {
     gptr<const float> x, y, z, nx, ny, nz;
     gptr<const int> mat;
@@ -125,15 +132,17 @@ struct SonarDev {
     double sin_half_az, cos_half_az;
     int wide_cols;              // columns wider than 0.09 rad: offsets need the full arctangent
     float r_min_f, scale_r_f;
-    // Transposed fan operator (plans): the entries of operator row h are
-    // ft_ent[ft_ptr[h] .. ft_ptr[h + 1]), each {fan pixel, bilinear weight as
-    // float bits}, in a fixed order.  Plain layout: row h is bin h, pixel
-    // v * fan_w + u.  Mirrored layout (ft_mirror, even fan width): row
-    // i * ceil(N_phi / 2) + j is bin (i, j) and also stands for its mirror
-    // bin (i, N_phi-1-j), whose entries are the same weights at the mirrored
+    // Transposed fan operator (plans): the entries of cell h = i * ncol + j
+    // are ft_ent[ft_ptr[h] .. ft_ptr[h + 1]), in a fixed order: one for each fan
+    // pixel whose stencil has range row i and the azimuth columns j and j + 1,
+    // with its weights on bins (i, j) and (i, j + 1).  Bin (i, j) is the sum of
+    // cell j's first weights and, for j > 0, cell j - 1's second ones.  Plain
+    // layout: ncol = N_phi, pixel v * fan_w + u.  Mirrored layout (ft_mirror, even
+    // fan width): ncol = ceil(N_phi / 2), and row (i, j) also stands for its
+    // mirror bin (i, N_phi-1-j), whose weights are the same at the mirrored
     // pixels (v, fan_w-1-u); pixel packed as (v << 16) | u.  nullptr: none.
     gptr<const int> ft_ptr;
-    gptr<const uint2> ft_ent;
+    gptr<const FanEntry> ft_ent;
     int ft_mirror;
     // Range-wise normalisation: each range row of Q = G P over its maximum
     // (when positive).  saved_p: the forward's binned sums P [nb]; dldq: the
@@ -141,7 +150,7 @@ struct SonarDev {
     int range_norm;
     gptr<float> saved_p;
     gptr<float> dldq;
-    int n_fant_blocks;          // backward workgroups (kBlock * BPT operator rows each) through the operator
+    int n_fant_blocks;          // backward workgroups (kFantRows * BPT operator rows each) through the operator
 };
 
 struct UwDev {

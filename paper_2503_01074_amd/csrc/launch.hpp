@@ -49,8 +49,8 @@ struct SonarGrid {
     int max_tile_bins_b; // largest backward tile of a frame, in bins
     int all_saved;       // every frame with a fan gradient has saved fan stencils
     int max_n_az;        // widest polar grid of a frame (azimuth cells)
-    int fant_blocks;     // backward workgroups of kBlock * fant_bpt bins over all frames (transposed fan operator)
-    int fant_bpt;        // bins per thread of those workgroups: 1, 2 or 4
+    int fant_blocks;     // backward workgroups of kFantRows * fant_bpt operator rows over all frames (transposed fan operator)
+    int fant_bpt;        // operator rows per thread of those workgroups: 1, 2 or 4
     int use_fant;        // backward through the frames' transposed fan operators instead of polar tiles
     int fant_mirror;     // some frame's operator has the mirrored layout
     int row_blocks;      // backward: one workgroup per range row of the range-normalised frames
@@ -61,6 +61,9 @@ struct SonarGrid {
 };
 
 constexpr int kBwdThreads = 512;   // threads of a backward polar-tile workgroup
+// operator rows a kBlock-thread workgroup of k_fant_bwd takes (times rows per
+// thread): the first lane of each wave takes the cell before the wave's rows
+constexpr int kFantRows = kBlock / kWave * (kWave - 1);
 
 // Camera frames carried along in the forward sonar launches of a plan
 // with both kinds of frames: device frame table, workgroups (kBlock threads

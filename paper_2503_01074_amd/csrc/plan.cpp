@@ -43,7 +43,7 @@ struct oceansim_plan {
     // (nullptr where a frame has none)
     char *fant_mem = nullptr;
     std::vector<const int *> fant_ptr;
-    std::vector<const uint2 *> fant_ent;
+    std::vector<const FanEntry *> fant_ent;
     char *ws_sf = nullptr, *ws_sb = nullptr, *ws_uf = nullptr, *ws_ub = nullptr;
     hipStream_t cap = nullptr;   // capture stream (default priority)
     // with both kinds of frames the camera frames ride along in the forward
@@ -593,8 +593,10 @@ struct HostRec {
 };
 
 // Visits the entries of one frame's transposed operator in pixel order:
-// fn(bin, pixel row v, pixel column u, weight).  The corners and the mirror
-// pixel follow the backward tile kernel's reading of a saved stencil.
+// fn(range row i, first column j0, pixel row v, pixel column u, weight on bin
+// (i, j0), weight on bin (i, j0 + 1)); a grid of one column has no second bin
+// (weight 0).  The corners and the mirror pixel follow the backward tile
+// kernel's reading of a saved stencil.
 template <class Fn>
 void for_each_entry(const oceansim_sonar_frame &f, const std::vector<HostRec> &recs, Fn fn) {
     const int W = f.fan_w, half_w = (f.fan_w + 1) / 2, n_az = f.n_azimuth;
@@ -616,10 +618,7 @@ void for_each_entry(const oceansim_sonar_frame &f, const std::vector<HostRec> &r
                 const int pu = side == 0 ? u : um;
                 for (int a = 0; a < (one_row ? 1 : 2); ++a) {
                     const double wa = a == 0 ? omt : t;
-                    for (int c = 0; c < (one_col ? 1 : 2); ++c) {
-                        const double wc = c == 0 ? omsw : sw;
-                        fn((long long)(r.i0 + a) * n_az + j0 + c, v, pu, (float)(wa * wc));
-                    }
+                    fn(r.i0 + a, j0, v, pu, (float)(wa * (double)omsw), one_col ? 0.0f : (float)(wa * (double)sw));
                 }
             }
         }
@@ -682,7 +681,7 @@ int build_fan_transposes(oceansim_plan *p, hipStream_t st) {
     if (e != hipSuccess) return hip_fail(e, "fan stencils");
     // row-major layout: counts, offsets, then the entries in pixel order
     std::vector<std::vector<int>> ptr(need.size());
-    std::vector<std::vector<uint2>> ent(need.size());
+    std::vector<std::vector<FanEntry>> ent(need.size());
     size_t bytes = 0;
     std::vector<size_t> off_ptr(need.size()), off_ent(need.size());
     for (size_t k = 0; k < need.size(); ++k) {
@@ -691,38 +690,31 @@ int build_fan_transposes(oceansim_plan *p, hipStream_t st) {
         const bool mirror = fan_operator_layout(f) == 2;
         const int n_az = f.n_azimuth, ncol = mirror ? (n_az + 1) / 2 : n_az;
         const long long nrow = (long long)f.n_range * ncol;
-        // operator row of bin b; -1: a mirror bin, read through its partner
-        auto row_of = [&](long long b) -> long long {
-            if (!mirror) return b;
-            const long long i = b / n_az, j = b - i * n_az;
-            return j < ncol ? i * ncol + j : -1;
-        };
+        // A cell is in the operator if its first bin has a row (mirrored layout:
+        // the others are read through their partners).  The size limit counts
+        // the weights on rows.
         std::vector<int> &P = ptr[k];
         P.assign(nrow + 1, 0);
-        long long total = 0;
-        for_each_entry(f, recs[k], [&](long long b, int, int, float) {
-            const long long h = row_of(b);
-            if (h < 0) return;
-            ++P[h + 1];
-            ++total;
+        long long weights = 0;
+        for_each_entry(f, recs[k], [&](int i, int j0, int, int, float, float) {
+            if (j0 >= ncol) return;
+            ++P[(long long)i * ncol + j0 + 1];
+            weights += j0 + 1 < ncol ? 2 : 1;
         });
-        if (total > INT32_MAX || (long long)f.fan_h * f.fan_w > INT32_MAX)
+        if (weights > INT32_MAX || (long long)f.fan_h * f.fan_w > INT32_MAX)
             return fail(OCEANSIM_E_UNSUPPORTED, "frame %d: fan operator too large", need[k]);
         for (long long h = 0; h < nrow; ++h) P[h + 1] += P[h];
         std::vector<int> cur(P.begin(), P.end() - 1);
-        ent[k].resize((size_t)total);
-        for_each_entry(f, recs[k], [&](long long b, int v, int u, float w) {
-            const long long h = row_of(b);
-            if (h < 0) return;
-            uint32_t wb;
-            std::memcpy(&wb, &w, 4);
+        ent[k].resize((size_t)P[nrow]);
+        for_each_entry(f, recs[k], [&](int i, int j0, int v, int u, float w0, float w1) {
+            if (j0 >= ncol) return;
             const unsigned pix = mirror ? ((unsigned)v << 16) | (unsigned)u : (unsigned)((long long)v * f.fan_w + u);
-            ent[k][cur[h]++] = make_uint2(pix, wb);
+            ent[k][cur[(long long)i * ncol + j0]++] = FanEntry{pix, w0, w1};
         });
         off_ptr[k] = bytes;
         bytes = (bytes + sizeof(int) * P.size() + kWsAlign - 1) / kWsAlign * kWsAlign;
         off_ent[k] = bytes;
-        bytes = (bytes + sizeof(uint2) * std::max<size_t>(1, ent[k].size()) + kWsAlign - 1) / kWsAlign * kWsAlign;
+        bytes = (bytes + sizeof(FanEntry) * std::max<size_t>(1, ent[k].size()) + kWsAlign - 1) / kWsAlign * kWsAlign;
     }
     e = hipMalloc(&p->fant_mem, bytes);
     if (e != hipSuccess) return hip_fail(e, "fan operator memory");
@@ -735,10 +727,10 @@ int build_fan_transposes(oceansim_plan *p, hipStream_t st) {
         e = hipMemcpyAsync(p->fant_mem + off_ptr[k], ptr[k].data(), sizeof(int) * ptr[k].size(),
                            hipMemcpyHostToDevice, st);
         if (e == hipSuccess && !ent[k].empty())
-            e = hipMemcpyAsync(p->fant_mem + off_ent[k], ent[k].data(), sizeof(uint2) * ent[k].size(),
+            e = hipMemcpyAsync(p->fant_mem + off_ent[k], ent[k].data(), sizeof(FanEntry) * ent[k].size(),
                                hipMemcpyHostToDevice, st);
         p->fant_ptr[need[k]] = reinterpret_cast<const int *>(p->fant_mem + off_ptr[k]);
-        p->fant_ent[need[k]] = reinterpret_cast<const uint2 *>(p->fant_mem + off_ent[k]);
+        p->fant_ent[need[k]] = reinterpret_cast<const FanEntry *>(p->fant_mem + off_ent[k]);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e, "fan operator upload");

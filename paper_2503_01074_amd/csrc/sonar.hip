@@ -1702,36 +1702,58 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
 
 // ---------------------------------------------------------------------------
 // k_fant_bwd: the polar gradient through the frames' transposed fan operators
-// (plans), BPT consecutive bins per thread: dL/dI[b] is the sum of weight *
-// dL/dF over the bin's entries, in FP64 and in the entries' fixed order
-// (each product of two floats is exact in FP64), plus the direct polar
+// (plans), BPT consecutive operator rows per thread: dL/dI[b] is the sum of
+// weight * dL/dF over the bin's fan pixels, in FP64 and in the entries' fixed
+// order (each product of two floats is exact in FP64), plus the direct polar
 // gradient; then the adjoint of Eq. (3)-(4) as in the tile epilogue.  No
 // candidate search, no fixed-point scale, no workgroup barrier before the
 // partial sums.
 //
-// The entries of a wave's 64 * BPT consecutive bins are contiguous: the wave
-// reads them in coalesced 64-entry chunks (lane k takes entry k of a chunk),
-// so the loads of one instruction are one span of 512 bytes and its fan
-// gathers are the neighbouring pixels of neighbouring bins; the products go
-// to the wave's slice of LDS, and each lane then sums its own bins' runs.
-// More bins per thread amortise the workgroup's fixed costs (frame lookup,
-// pointer loads, partial sums) where there are many bins to share the chip.
+// The kernel is bound by its gathers and by the latency of its chain of loads,
+// so the operator is kept by cells, not by bins: a fan pixel lies between two
+// azimuth columns, and its entry carries its weights on both, so that the
+// pixel is gathered once for the two.  A lane sums its own cells' entries
+// for both bins and hands the second sum of its last cell to the next lane; the first
+// lane of a wave takes the cell before the wave's rows and has no rows
+// itself.  The entries of a wave's cells are contiguous: the wave reads them
+// in coalesced 64-entry chunks (lane k takes entry k of a chunk), so its fan
+// gathers are the neighbouring pixels of neighbouring bins; weights and pixels go
+// to the wave's slice of LDS, and each lane then sums its own cells' runs while the
+// next round's entries are on their way.
 // With a mirrored operator (even fan width) a thread's rows are bins of the
 // left half of the azimuth columns: each entry is gathered at its pixel and
 // at the mirrored pixel, giving the row's bin and its mirror bin at once from
 // half the operator bytes.
+//
+// Against entries by bins, multiplied before LDS (a frame of 1024 x 1024 bins
+// and as dense a fan; 12 of them; 20 of 512 x 512): 17.8, 130, 52 us -> 16.7,
+// 111, 52 with 0.6 of the cache accesses.  Two chunks a round keep eight waves
+// on a SIMD (56 registers); four 16.6, 120, 53.  Neighbouring range rows read
+// the same fan lines, so runs of 16 workgroups go to one XCD: 15.8, 107, 43.5
+// (8: 16.6, 108, 44.8; 64: 15.7, 108, 47.4).  What bounds it now is the VALU,
+// mostly the speckle of every bin and the lanes' unequal runs.
 // ---------------------------------------------------------------------------
-constexpr int kFantChunks = 8;   // 64-entry chunks staged per round (512 entries per wave; mirrored: 256)
+constexpr int kFantChunks = 2;    // 64-entry chunks staged per round
+constexpr int kFantXcdRun = 16;   // consecutive workgroups one XCD takes
 constexpr size_t kFuseLdsBytes = 16384;   // LDS of a return-gather workgroup that camera workgroups may share
+
+// The value of the lane before (0 in lane 0).
+__device__ __forceinline__ double wave_shift_up(double v) {
+    constexpr int kWaveShr1 = 0x138;
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, kWaveShr1, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), kWaveShr1, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 
 // MIRROR: the batch has mirrored operators (their rows produce two bins;
 // without any, the kernel keeps one output per row and fewer registers).
 template <class Src, int BPT, bool MIRROR>
 __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_sonar_params *params, double *part,
                                                      int n_slots, float *grad_refl_zero, int n_mat_zero) {
-    __shared__ double prod[kBlock / kWave][kFantChunks * kWave];
+    __shared__ float4 staged[kBlock / kWave][kFantChunks * kWave];   // {w0, w1, dL/dF, dL/dF mirrored}
     int local;
-    const int bid = blockIdx.x;
+    const int bid = xcd_grouped_id<kFantXcdRun>(blockIdx.x, gridDim.x);
     const int fi = src.locate(bid, KFANT, local);
     const SonarDev f = src.frame(fi);
     const int tid = threadIdx.x;
@@ -1742,46 +1764,71 @@ __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_son
     const bool mir = MIRROR && f.ft_mirror != 0 && f.ft_ptr;
     const int ncol = mir ? (f.n_az + 1) >> 1 : f.n_az;
     const int nrow = f.n_range * ncol;
-    const int h0 = (local * kBlock + tid) * BPT;   // this thread's first row
+    // the wave's rows [wb, wb + (kWave - 1) * BPT): uniform, so what depends on
+    // them alone stays in scalar registers; this lane's first row (lane 0: the
+    // cells before the wave's rows)
+    constexpr int kWaveRows = (kWave - 1) * BPT;
+    const int wb = (local * (kBlock / kWave) + __builtin_amdgcn_readfirstlane(wave)) * kWaveRows;
+    const int h0 = wb + (lane - 1) * BPT;
     // Loads first, without branches (indices clamped), so that they are in
     // flight together while the speckle factors are computed: the parameter
     // row (before any store, so it may come through the scalar cache), this
-    // lane's rows' operator pointers and the direct polar gradient.
+    // lane's cells' operator pointers and the direct polar gradient.
     const oceansim_sonar_params pr = params[f.param_row];
-    // the wave's span of entries [w_lo, w_hi): uniform addresses, so scalar
-    // loads, and the only ones the entry loads wait for
-    const int wb = (local * kBlock + __builtin_amdgcn_readfirstlane(wave) * kWave) * BPT;
+    // the wave's span of entries [w_lo, w_hi), from the cell before its rows:
+    // scalar loads, and the only ones the entry loads wait for
+    const int first = wb > nrow ? nrow : wb > 0 ? wb - 1 : 0;
+    const int last = wb + kWaveRows < nrow ? wb + kWaveRows : nrow;
     int w_lo = 0, w_hi = 0;
     if (f.ft_ptr) {
-        w_lo = f.ft_ptr[wb < nrow ? wb : nrow];
-        w_hi = f.ft_ptr[wb + kWave * BPT < nrow ? wb + kWave * BPT : nrow];
+        w_lo = f.ft_ptr[first];
+        w_hi = f.ft_ptr[last];
     }
-    int p[BPT + 1];   // this lane's rows' entries start at p[0..BPT-1] and end at p[BPT]
+    int p[BPT + 1];   // this lane's cells' entries start at p[0..BPT-1] and end at p[BPT]
 #pragma unroll
-    for (int m = 0; m <= BPT; ++m) p[m] = f.ft_ptr ? f.ft_ptr[h0 + m < nrow ? h0 + m : nrow] : 0;
-    // output bins: ob[m] is row m's own bin, ob[BPT + m] (MIRROR) its mirror bin (-1:
-    // none, plain layout or a middle column that is its own mirror); -1 past
-    // the end
-    int ob[MIRROR ? NO : 1];
-    if constexpr (MIRROR) {
-        int i = h0 / ncol, j = h0 - i * ncol;
+    for (int m = 0; m <= BPT; ++m) {
+        const int h = h0 + m < first ? first : h0 + m < last ? h0 + m : last;
+        p[m] = f.ft_ptr ? f.ft_ptr[h] : 0;
+    }
+    // Range row and column of row h0 + m (of no use in lane 0).  A wave whose
+    // rows lie in at most two range rows divides once, in scalar registers, and not in every lane.
+    int ri[BPT], cj[BPT];
+    {
+        int i, j;
+        if (ncol >= kWaveRows) {
+            i = wb / ncol;
+            j = wb - i * ncol + (lane - 1) * BPT;
+            if (j >= ncol) {
+                j -= ncol;
+                ++i;
+            }
+        } else {
+            i = h0 / ncol;
+            j = h0 - i * ncol;
+        }
 #pragma unroll
         for (int m = 0; m < BPT; ++m) {
-            const bool in = h0 + m < nrow;
-            const int jm = f.n_az - 1 - j;
-            ob[m] = in ? i * f.n_az + j : -1;
-            ob[BPT + m] = in && mir && jm != j ? i * f.n_az + jm : -1;
+            ri[m] = i;
+            cj[m] = j;
             if (++j == ncol) {
                 j = 0;
                 ++i;
             }
         }
     }
-    // output bin k (plain rows are the bins themselves)
-    auto out_bin = [&](int k) __attribute__((always_inline)) -> int {
-        if constexpr (MIRROR) return ob[k];
-        else return h0 + k < nrow ? h0 + k : -1;
-    };
+    // output bins: ob[m] is row m's own bin, ob[BPT + m] (MIRROR) its mirror bin (-1:
+    // none, plain layout or a middle column that is its own mirror); -1 past
+    // the end
+    int ob[NO];
+#pragma unroll
+    for (int m = 0; m < BPT; ++m) {
+        const bool in = lane > 0 && h0 + m < nrow;
+        ob[m] = in ? ri[m] * f.n_az + cj[m] : -1;
+        if constexpr (MIRROR) {
+            const int jm = f.n_az - 1 - cj[m];
+            ob[BPT + m] = in && mir && jm != cj[m] ? ri[m] * f.n_az + jm : -1;
+        }
+    }
     // (without a polar gradient the load reads this frame's own gradient
     // buffer, a valid address, and the value is discarded: a select, not a
     // branch that would wait for the load)
@@ -1791,128 +1838,146 @@ __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_son
         const gptr<const float> src_pol = has ? f.grad_polar : (gptr<const float>)f.grad_img;
 #pragma unroll
         for (int k = 0; k < NO; ++k) {
-            const int bk = out_bin(k);
-            const float v = src_pol[bk >= 0 ? bk : 0];
+            const float v = src_pol[ob[k] >= 0 ? ob[k] : 0];
             gpol[k] = has ? v : 0.0f;
         }
     }
     // the atomic reflectivity path (many materials) accumulates into a zeroed table
     if (grad_refl_zero)
         for (int k = bid * kBlock + tid; k < n_mat_zero; k += (int)gridDim.x * kBlock) grad_refl_zero[k] = 0.0f;
+    // The entries of the round that starts at r0.  Every lane loads (past the
+    // end it re-reads the wave's last entry, which no cell sums); a chunk pair
+    // that is wholly past the end is not read.
+    unsigned px[kFantChunks];
+    float2 w[kFantChunks];
+    auto load_entries = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < kFantChunks; ++c)
+            if (c % 2 == 0 ? r0 + c * kWave < w_hi : r0 + (c - 1) * kWave < w_hi) {
+                const int e = r0 + c * kWave + lane;
+                const gptr<const FanEntry> q = f.ft_ent + (e < w_hi ? e : w_hi - 1);
+                px[c] = q->pixel;
+                w[c] = make_float2(q->w0, q->w1);
+            }
+    };
+    load_entries(w_lo);
     // per output bin, the factors of the adjoint of Eq. (3)-(4): R E rho and
-    // phi^2; computed once, while the first round's gathers are in flight
-    float fac[NO], phi2[NO];
-    auto speckle_factors = [&]() __attribute__((always_inline)) {
+    // phi^2; computed while the first round's entries are in flight
+    float fac[NO], phi2[BPT];
+#pragma unroll
+    for (int k = 0; k < NO; ++k) fac[k] = phi2[k % BPT] = 0.0f;
+    if (f.speckle != SPECKLE_OFF) {
+        // a bin and its mirror have the same range and opposite azimuths: the
+        // same ramp and beam pattern
         const AddCtx ctx{pr.sigma_sa, 1.0f / pr.sigma_phi};
         Words wd{0u, 0u, 0u, 0u};
         int wq = -1;
-#pragma unroll
-        for (int k = 0; k < NO; ++k) {
-            const int b = out_bin(k);
-            fac[k] = phi2[k] = 0.0f;
-            if (f.speckle != SPECKLE_OFF && b >= 0) {
-                // the bin's Philox word is the one its forward tile drew
-                if ((b >> 2) != wq) {
-                    wq = b >> 2;
-                    wd = philox((uint32_t)wq, f.frame_id, 0u, 0u, f.seed_lo, f.seed_hi);
-                }
-                const int i = b / f.n_az, j = b - i * f.n_az;
-                float E, rho, R, phi;
-                additive_term(f, ctx, i, j, pick(wd, (uint32_t)(b & 3)), E, rho, R, phi);
-                fac[k] = R * E * rho;
-                phi2[k] = phi * phi;
+        // the bin's Philox word is the one its forward tile drew
+        auto word = [&](int b) __attribute__((always_inline)) -> uint32_t {
+            if ((b >> 2) != wq) {
+                wq = b >> 2;
+                wd = philox((uint32_t)wq, f.frame_id, 0u, 0u, f.seed_lo, f.seed_hi);
             }
+            return pick(wd, (uint32_t)(b & 3));
+        };
+#pragma unroll
+        for (int m = 0; m < BPT; ++m) {
+            float E, rho, R, phi;
+            additive_term(f, ctx, ri[m], cj[m], word(ob[m]), E, rho, R, phi);
+            fac[m] = R * E * rho;
+            phi2[m] = phi * phi;
+            if constexpr (MIRROR) fac[BPT + m] = R * E * rayleigh_of_word(word(ob[BPT + m]));
         }
-    };
-    bool have_factors = false;
-    double gs[NO];
+    }
+    double gs[NO], carry[2] = {0.0, 0.0};   // carry: on the column after the last row (own, mirrored)
 #pragma unroll
     for (int k = 0; k < NO; ++k) gs[k] = 0.0;
-    // Rounds of NC coalesced 64-entry chunks; MIR: each entry also gathers
-    // the mirrored pixel, whose products fill the slice's second half.
-    auto rounds = [&](auto nc, auto mirror) __attribute__((always_inline)) {
-        constexpr int NC = decltype(nc)::value;
+    auto rounds = [&](auto mirror) __attribute__((always_inline)) {
         constexpr bool MIR = decltype(mirror)::value;
-        double *slice = prod[wave];
-        for (int r0 = w_lo; r0 < w_hi; r0 += NC * kWave) {
-            // Every lane loads (past the end it re-reads the wave's last entry,
-            // whose product no row sums): no branch in the unrolled loads, so
-            // all the chunk's loads, then all its gathers, are in flight together.
-            uint2 en[NC];
+        float4 *slice = staged[wave];
+        for (int r0 = w_lo; r0 < w_hi; r0 += kFantChunks * kWave) {
+            float gv[kFantChunks], gm[kFantChunks];
+            if (r0 != w_lo) load_entries(r0);
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const int e = r0 + c * kWave + lane;
-                en[c] = gload(f.ft_ent + (e < w_hi ? e : w_hi - 1));
-            }
-            if (!have_factors) {   // uniform: under the first round's entry loads
-                speckle_factors();
-                have_factors = true;
-            }
-            float gv[NC], gm[NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                if constexpr (MIR) {
-                    const unsigned u = en[c].x & 0xffffu;
-                    const unsigned row = __umul24(en[c].x >> 16, (unsigned)f.fan_w);   // < 2^31
-                    gv[c] = f.grad_fan[row + u];
-                    gm[c] = f.grad_fan[row + ((unsigned)f.fan_w - 1u - u)];
-                } else {
-                    gv[c] = f.grad_fan[(long long)en[c].x];
+            for (int c = 0; c < kFantChunks; ++c)
+                if (r0 + (c & ~1) * kWave < w_hi) {
+                    if constexpr (MIR) {
+                        const unsigned u = px[c] & 0xffffu;
+                        const unsigned row = __umul24(px[c] >> 16, (unsigned)f.fan_w);   // < 2^31
+                        gv[c] = f.grad_fan[row + u];
+                        gm[c] = f.grad_fan[row + ((unsigned)f.fan_w - 1u - u)];
+                    } else {
+                        gv[c] = f.grad_fan[(long long)px[c]];
+                        gm[c] = 0.0f;
+                    }
                 }
-            }
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const double w = (double)__uint_as_float(en[c].y);
-                slice[c * kWave + lane] = w * (double)gv[c];
-                if constexpr (MIR) slice[(NC + c) * kWave + lane] = w * (double)gm[c];
-            }
+            for (int c = 0; c < kFantChunks; ++c)
+                if (r0 + (c & ~1) * kWave < w_hi)
+                    slice[c * kWave + lane] = make_float4(w[c].x, w[c].y, gv[c], gm[c]);
             // the wave's own LDS writes, then its reads (no other wave touches the slice)
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             const int a = p[0] > r0 ? p[0] : r0;
-            const int z = p[BPT] < r0 + NC * kWave ? p[BPT] : r0 + NC * kWave;
+            const int z = p[BPT] < r0 + kFantChunks * kWave ? p[BPT] : r0 + kFantChunks * kWave;
             for (int e = a; e < z; ++e) {
-                const double v = slice[e - r0];
-                int m = 0;
+                const float4 q = slice[e - r0];
+                if constexpr (BPT == 1) {
+                    gs[0] = fma((double)q.x, (double)q.z, gs[0]);
+                    carry[0] = fma((double)q.y, (double)q.z, carry[0]);
+                    if constexpr (MIR) {
+                        gs[1] = fma((double)q.x, (double)q.w, gs[1]);
+                        carry[1] = fma((double)q.y, (double)q.w, carry[1]);
+                    }
+                } else {
+                    int m = 0;
 #pragma unroll
-                for (int k = 1; k < BPT; ++k) m += e >= p[k] ? 1 : 0;
+                    for (int k = 1; k < BPT; ++k) m += e >= p[k] ? 1 : 0;
 #pragma unroll
-                for (int k = 0; k < BPT; ++k) gs[k] += m == k ? v : 0.0;
-                if constexpr (MIR && MIRROR) {
-                    const double vm = slice[NC * kWave + e - r0];
+                    for (int s = 0; s < (MIR ? 2 : 1); ++s) {
+                        const double g = s == 0 ? (double)q.z : (double)q.w;
+                        const double v0 = (double)q.x * g, v1 = (double)q.y * g;
 #pragma unroll
-                    for (int k = 0; k < BPT; ++k) gs[BPT + k] += m == k ? vm : 0.0;
+                        for (int k = 0; k < BPT; ++k) {
+                            gs[s * BPT + k] += m == k ? v0 : 0.0;
+                            // column 0 has no cell before it
+                            if (k > 0) gs[s * BPT + k] += m == k - 1 && cj[k] != 0 ? v1 : 0.0;
+                        }
+                        carry[s] += m == BPT - 1 ? v1 : 0.0;
+                    }
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
+        const double before = wave_shift_up(carry[0]);
+        if (cj[0] != 0) gs[0] += before;
+        if constexpr (MIR) {
+            const double before_m = wave_shift_up(carry[1]);
+            if (cj[0] != 0) gs[BPT] += before_m;
+        }
     };
     if (f.ft_ptr) {
-        if (mir)
-            rounds(std::integral_constant<int, kFantChunks / 2>{}, std::integral_constant<bool, MIRROR>{});
-        else
-            rounds(std::integral_constant<int, kFantChunks>{}, std::false_type{});
+        if constexpr (MIRROR) {
+            if (mir) rounds(std::true_type{});
+            else rounds(std::false_type{});
+        } else {
+            rounds(std::false_type{});
+        }
     }
-    if (!have_factors) speckle_factors();
     double g_sphi = 0.0, g_ssa = 0.0;
-    const double dsphi = 0.5 * (double)pr.sigma_sa / ((double)pr.sigma_phi * (double)pr.sigma_phi);
 #pragma unroll
     for (int k = 0; k < NO; ++k) {
-        const int b = out_bin(k);
-        if (b < 0) {
-            if constexpr (MIRROR) continue;   // a missing mirror bin; later rows may follow
-            else break;                       // past the end
-        }
+        if (ob[k] < 0) continue;   // none here; later rows may follow
         const double g = gs[k] + (double)gpol[k];
-        f.grad_img[b] = (float)g;
+        f.grad_img[ob[k]] = (float)g;
         // d add / d sigma_sa and d add / d sigma_phi of Eq. (3)-(4) (zero
         // factors without speckle)
         const double t = g * (double)fac[k];
         g_ssa += 0.5 * t;
-        g_sphi += t * dsphi * (double)phi2[k];
+        g_sphi += t * (double)phi2[k % BPT];
     }
     __shared__ double red2[2 * (kBlock / kWave)];
     const double sums[2] = {g_sphi, g_ssa};
@@ -1921,7 +1986,9 @@ __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_son
         reinterpret_cast<int *>(part + 5LL * n_slots)[bid] = f.param_row;
         part[0LL * n_slots + bid] = 0.0;
         part[1LL * n_slots + bid] = 0.0;
-        part[2LL * n_slots + bid] = tot;
+        // the factor of d add / d sigma_phi that all bins share
+        const double dsphi = 0.5 * (double)pr.sigma_sa / ((double)pr.sigma_phi * (double)pr.sigma_phi);
+        part[2LL * n_slots + bid] = tot * dsphi;
         part[4LL * n_slots + bid] = 0.0;
     }
     if (tid == 1) part[3LL * n_slots + bid] = tot;

@@ -250,3 +250,65 @@ def test_operator_rows_per_thread_follow_the_fan_density(n_bins, side, block_bin
     plan.close()
     o_refl, _, c_refl, _ = _oracle([W.SonarFrame(spec, hits)], hits.refl, [gpol], [gfan])
     assert_grad_cond(g_refl, o_refl, c_refl, what="refl")
+
+
+@pytest.mark.parametrize("n_range,n_az", [(3, 62), (5, 63), (5, 64), (4, 65), (3, 124), (4, 125), (5, 126), (4, 127),
+                                          (5, 128), (2, 253), (3, 504), (7, 505), (64, 3), (90, 2)])
+@pytest.mark.parametrize("fan", [(50, 120), (50, 121), (7, 10)])
+def test_cells_at_wave_and_workgroup_edges(n_range, n_az, fan):
+    """A wave takes 63 operator rows and the cell before them: range rows (and
+    mirrored halves of them) of just under, exactly and just over that many
+    rows, ends of waves and workgroups within a range row and between two, and
+    fans with many and with hardly any pixels per bin."""
+    st = W.Stream(8800 + n_az, n_range)
+    H, Wd = fan
+    frames = [_frame(st, n_range, n_az, H, Wd, 1500), _frame(st, n_range, n_az, H + 3, Wd, 900, frame_id=1,
+                                                            mode=W.SPECKLE_GAMMA, r_max=11.0)]
+    refl = frames[0].hits.refl
+    for f in frames:
+        f.hits.refl = refl
+    gpol = [W.loss_weights((8801, k), (n_range, n_az)) for k in range(2)]
+    gfan = [W.loss_weights((8802, k), (f.spec.fan_h, f.spec.fan_w)) for k, f in enumerate(frames)]
+    g_refl, g_par = _plan_backward(frames, refl, gpol, gfan)
+    o_refl, o_par, c_refl, c_par = _oracle(frames, refl, gpol, gfan)
+    assert_grad_cond(g_refl, o_refl, c_refl, what="refl")
+    assert_grad_cond(g_par[0, :5], o_par[0], c_par[0], what="params")
+
+
+def test_unused_fan_gradient_stays_in_its_cell():
+    """A fan pixel's gradient reaches its own bins alone, also where the next
+    lane, wave or range row sums beside it: bins that no fan pixel of a NaN
+    gradient reads keep their gradient exactly."""
+    import torch
+    import paper_2503_01074_amd as osm
+    st = W.Stream(8900, 1)
+    for n_range, n_az, Wd in ((6, 126, 140), (6, 126, 141), (5, 64, 90), (40, 3, 30)):
+        f = _frame(st, n_range, n_az, 40, Wd, 4000, mode=W.SPECKLE_OFF)
+        # every return its own material: the gradient of a reflectivity is its bin's
+        f.hits.mat[:] = np.arange(len(f.hits.mat))
+        refl = np.full((len(f.hits.mat),), 0.5, np.float32)
+        gfan = W.loss_weights((8901, n_az), (40, Wd))
+        got = []
+        for v, u in ((None, None), (20, 3), (20, Wd - 4), (33, Wd // 2), (12, Wd // 4)):
+            g = gfan.copy()
+            if v is not None:
+                g[v, u] = np.nan
+            plan = osm.Plan([(osm.SonarGeometry.from_spec(f.spec), osm.DeviceHits.from_host(f.hits))],
+                            sonar_params=osm.sonar_params([osm.sonar_params_from_spec(f.spec)]),
+                            refl=torch.as_tensor(refl).cuda(), backward=True, bins=True)
+            plan.sonar_out[0]["grad_polar"].zero_()
+            plan.sonar_out[0]["grad_fan"].copy_(torch.as_tensor(g))
+            plan.forward()
+            plan.backward()
+            torch.cuda.synchronize()
+            got.append((plan.grad_refl.cpu().numpy(), plan.sonar_out[0]["bins"].cpu().numpy()))
+            plan.close()
+        base, bins = got[0]
+        assert np.isfinite(base).all()
+        for g, _ in got[1:]:
+            bad = ~np.isfinite(g)
+            hit = np.unique(bins[bad])
+            # one pixel's stencil: two neighbouring columns of two range rows
+            assert len(hit) <= 4 and (len(hit) == 0 or (hit % n_az).max() - (hit % n_az).min() <= 1)
+            assert (np.unique(hit // n_az).size <= 2)
+            np.testing.assert_array_equal(g[~bad], base[~bad])
