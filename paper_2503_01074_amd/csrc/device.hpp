@@ -441,6 +441,24 @@ __device__ __forceinline__ float return_intensity(const SonarDev &f, float xf, f
 
 // Additive speckle geometry of bin (i, j): R_i = r_i^2 / r_max^2 and the
 // bin-centre azimuth phi_j (Eq. 3).
+// b / n and the remainder for 0 <= b < 2^24 (a polar bin) by inv = 1.0f / n, a
+// third of an integer division's instructions: b is exact in float, and the
+// product, two roundings of 2^-24 away from the quotient, within 2/3 of it for
+// n >= 3 (the quotient is below 2^24 / 3) and exact for n = 1 and 2, so one step
+// either way corrects it.
+__host__ __device__ __forceinline__ int bin_row(int b, int n, float inv, int &column) {
+    int i = (int)((float)b * inv);
+    int j = b - i * n;
+    if (j < 0) {
+        --i;
+        j += n;
+    } else if (j >= n) {
+        ++i;
+        j -= n;
+    }
+    column = j;
+    return i;
+}
 __device__ __forceinline__ float range_ramp(const SonarDev &f, int i) {
     double ri = f.r_min + ((double)i + 0.5) * f.dr;
     double q = ri * f.inv_r_max;

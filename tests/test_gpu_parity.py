@@ -593,3 +593,24 @@ def test_sonar_backward_many_frames_and_rows(per_return_refl):
     for r in range(4):
         assert_grad_cond(g_par[r, :5], o_par[r], c_par[r], what="row %d" % r)
     assert np.all(g_par[:, 5:] == 0)
+
+
+@pytest.mark.parametrize("n_az", [1, 2, 3, 4, 5, 7, 8, 12, 62, 64, 100, 252, 255, 256, 257, 1000, 1001, 1022, 2047, 4095])
+def test_groups_of_four_bins_and_range_rows(n_az):
+    """The additive term is drawn for groups of four bins: rows whose length is
+    a multiple of four (a group lies in one row) and lengths around it (groups
+    over two or more rows), in frames without and with returns."""
+    n_range = max(3, 6000 // n_az)
+    st = W.Stream(1450, n_az)
+    specs = [W.SonarSpec(r_min=0.5, r_max=10.0, n_range=n_range, n_azimuth=n_az, speckle_mode=mode, sigma_sa=0.3,
+                         sigma_phi=0.4, sigma_sm=0.1, gamma_k=2, seed_lo=n_az, frame_id=k, alpha=0.05)
+             for k, mode in enumerate((W.SPECKLE_PAPER, W.SPECKLE_GAMMA))]
+    frames, refl = merged([W.SonarFrame(s, W.make_hits(st, s, n, n_materials=4)) for s, n in zip(specs, (1, 3000))])
+    got = gpu_forward(frames, refl, fan=False)
+    for k, f in enumerate(frames):
+        check_frame(got[k], oracle_forward(f, refl), "n_az %d frame %d" % (n_az, k), fan=False)
+    gpol = [W.loss_weights((1451, k), (n_range, n_az)) for k in range(2)]
+    g_refl, g_par = gpu_backward(frames, refl, gpol, [None, None])
+    o_refl, o_par, c_refl, c_par = oracle_backward(frames, refl, gpol, [None, None])
+    assert_grad_cond(g_refl, o_refl, c_refl, what="refl")
+    assert_grad_cond(g_par[0, :5], o_par, c_par, what="params")

@@ -241,3 +241,50 @@ def test_interleaving_by_ratio_is_a_bijection(tmp_path):
     assert r.returncode == 0, r.stderr[-3000:]
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
+
+
+ROW_PROGRAM = r"""
+#include "device.hpp"
+#include <cstdio>
+
+using namespace osim;
+
+int main() {
+    const int top = 1 << 24;
+    for (int n = 1; n < top; n += n < 4200 ? 1 : n / 97) {
+        const float inv = 1.0f / (float)n;
+        // every multiple of n (or a spread of them) and its neighbours, and the last bins
+        const long long rows = top / n, step = rows > 6000 ? rows / 3001 : 1;
+        for (long long i = 0; i <= rows; i += step)
+            for (int d = -2; d <= 2; ++d) {
+                const long long b = i * n + d;
+                if (b < 0 || b >= top) continue;
+                int j;
+                const int r = bin_row((int)b, n, inv, j);
+                if (r != (int)(b / n) || j != (int)(b % n)) { printf("n=%d b=%lld: %d %d\n", n, b, r, j); return 1; }
+            }
+        for (int b = top - 1; b > top - 9; --b) {
+            int j;
+            if (bin_row(b, n, inv, j) != b / n || j != b % n) { printf("n=%d b=%d\n", n, b); return 1; }
+        }
+    }
+    printf("ok\n");
+    return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="hipcc not available")
+def test_range_row_of_a_bin(tmp_path):
+    """Row and column of every bin a frame can have (below 2^24), by the
+    reciprocal of the row length."""
+    src = tmp_path / "rows.hip"
+    exe = tmp_path / "rows"
+    src.write_text(ROW_PROGRAM)
+    hipcc = HIPCC if os.path.exists(HIPCC) else shutil.which("hipcc")
+    r = subprocess.run([hipcc, "-x", "hip", "--cuda-host-only", "-std=c++17", "-O2", "-I", CSRC,
+                        "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
