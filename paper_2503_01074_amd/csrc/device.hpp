@@ -180,6 +180,18 @@ __host__ __device__ __forceinline__ int xcd_grouped_id(int b, int n) {
     return b / round * round + (b % kXcds) * G + (b / kXcds) % G;
 }
 
+// The same with the runs of round r dealt from XCD r on: where the work repeats
+// with a period that divides a round (fan tiles: a column of tiles is a whole
+// number of runs, and its middle costs most), every XCD still gets each part
+// of the period.  The last partial round keeps b.
+template <int G>
+__host__ __device__ __forceinline__ int xcd_rotated_id(int b, int n) {
+    constexpr int round = kXcds * G;
+    const int r = b / round;
+    if (b >= n / round * round) return b;
+    return r * round + ((b + r) % kXcds) * G + (b / kXcds) % G;
+}
+
 // Flat walk over NT segments laid end to end (segment c holds flat indices
 // [seg_end[c - 1], seg_end[c]), seg_end the inclusive prefix of the
 // lengths, total the last entry): a coarse map of 2 NT entries finds the

@@ -609,6 +609,16 @@ __device__ __forceinline__ float2 polar_pair_at(gptr<const float> base, int idx)
     return make_float2(v.x, v.y);
 }
 
+// Consecutive tiles (along a column of the fan) one XCD takes: they gather from
+// the same polar rows.  k_fan deals the runs rotated: a column of a 1024-row fan
+// is four runs, so that unrotated two XCDs had the quarter of every column
+// that lies wholly in the sector.  Frames of n x n bins, fan n x 2n, unrotated -> rotated:
+// 1 x 1024 11.8 -> 10.0 us, 8 x 1024 49.6 -> 40.0, 4 x 2048 94 -> 69, 20 x 512
+// 30.5 -> 29.2 (runs of 8 and 64 within 3 % of it; single tiles: 20 x 512 36).  Beside camera
+// blocks, which shift the runs themselves, rotation only costs: 8 x 1024 + 8
+// images of 1080p 147 -> 150, so k_fan_uw keeps the plain order.
+constexpr int kFanXcdRun = 16;
+
 // IMAGE = false: the stencil records alone (geometry only; the polar image is
 // not read and the fan is not written).
 template <class Src, bool IMAGE>
@@ -753,7 +763,7 @@ __device__ __forceinline__ void fan_block(const Src &src, int bid) {
 
 template <class Src, bool IMAGE = true>
 __global__ __launch_bounds__(kBlock) void k_fan(Src src) {
-    fan_block<Src, IMAGE>(src, xcd_grouped_id<16>(blockIdx.x, gridDim.x));
+    fan_block<Src, IMAGE>(src, xcd_rotated_id<kFanXcdRun>(blockIdx.x, gridDim.x));
 }
 
 // The fan and blocks [cam0, cam0 + n) of a plan's camera forward in one launch,
@@ -761,7 +771,7 @@ __global__ __launch_bounds__(kBlock) void k_fan(Src src) {
 // the fan waits on its gathers and its arithmetic, the camera on HBM.
 __global__ __launch_bounds__(kBlock) void k_fan_uw(Table<SonarDev> src, unsigned ratio, Table<UwDev> usrc,
                                                    const oceansim_water_params *wparams, int cam0) {
-    const FusedSlot slot = fused_slot_by_ratio((unsigned)xcd_grouped_id<16>(blockIdx.x, gridDim.x), ratio);
+    const FusedSlot slot = fused_slot_by_ratio((unsigned)xcd_grouped_id<kFanXcdRun>(blockIdx.x, gridDim.x), ratio);
     if (slot.cam)
         uw_fwd_block<Table<UwDev>, kBlock>(usrc, wparams, cam0 + slot.index, threadIdx.x);
     else
@@ -878,7 +888,9 @@ __device__ __forceinline__ void tile_bwd_block(const Src &src, const oceansim_so
     __shared__ int sh_shift;
 
     int local;
-    const int lid = xcd_grouped_id<8>(bid, n_blocks);   // also this tile's partial-sum slot
+    // rotated: 8 frames of 512 x 512 47 -> 42.5 us (xcd_grouped_id, whose rounds
+    // repeat with a frame's 128 tiles, gives each XCD one part of the range)
+    const int lid = xcd_rotated_id<8>(bid, n_blocks);   // also this tile's partial-sum slot
     const int fi = src.locate(lid, KTILEB, local);
     const SonarDev f = src.frame(fi);
     const int tile = f.n_tiles_b - 1 - local;   // outer tiles (most pixels) first

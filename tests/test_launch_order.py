@@ -288,3 +288,54 @@ def test_range_row_of_a_bin(tmp_path):
     assert r.returncode == 0, r.stderr[-3000:]
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
+
+
+ROTATED_PROGRAM = r"""
+#include "device.hpp"
+#include <cstdio>
+#include <vector>
+
+using namespace osim;
+
+template <int G>
+static int check(int n) {
+    std::vector<char> seen(n, 0);
+    for (int b = 0; b < n; ++b) {
+        const int x = xcd_rotated_id<G>(b, n);
+        if (x < 0 || x >= n || seen[x]++) return 1;
+    }
+    // each XCD (b % kXcds) takes a run of G consecutive ids per round, and the
+    // run's place within the round moves on by one from round to round
+    const int round = kXcds * G;
+    for (int r = 0; (r + 1) * round <= n; ++r)
+        for (int xcd = 0; xcd < kXcds; ++xcd)
+            for (int k = 0; k < G; ++k)
+                if (xcd_rotated_id<G>(r * round + xcd + k * kXcds, n) != r * round + (xcd + r) % kXcds * G + k) return 2;
+    return 0;
+}
+
+int main() {
+    for (int n = 0; n <= 4200; ++n) {
+        if (int e = check<8>(n)) { printf("<8> n=%d error %d\n", n, e); return 1; }
+        if (int e = check<16>(n)) { printf("<16> n=%d error %d\n", n, e); return 1; }
+    }
+    for (int n : {32768, 32771, 1000003})
+        if (check<8>(n) || check<16>(n)) { printf("n=%d\n", n); return 1; }
+    printf("ok\n");
+    return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="hipcc not available")
+def test_rotated_runs_are_a_bijection(tmp_path):
+    src = tmp_path / "rotated.hip"
+    exe = tmp_path / "rotated"
+    src.write_text(ROTATED_PROGRAM)
+    hipcc = HIPCC if os.path.exists(HIPCC) else shutil.which("hipcc")
+    r = subprocess.run([hipcc, "-x", "hip", "--cuda-host-only", "-std=c++17", "-O2", "-I", CSRC,
+                        "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
