@@ -614,3 +614,25 @@ def test_groups_of_four_bins_and_range_rows(n_az):
     o_refl, o_par, c_refl, c_par = oracle_backward(frames, refl, gpol, [None, None])
     assert_grad_cond(g_refl, o_refl, c_refl, what="refl")
     assert_grad_cond(g_par[0, :5], o_par, c_par, what="params")
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 15, 16, 17, 255, 256, 257, 511, 3839, 3840, 3841, 4095, 4096, 4097, 4352])
+def test_water_gradient_sums_of_any_number_of_partials(blocks):
+    """Constant images of `blocks` workgroups of 2048 pixels, on two parameter
+    rows: every partial sum is the same, so a partial missed or taken twice by
+    the reduction shows as 1 / blocks of the result (the pixels' FP32 terms are
+    within 1e-6 of theirs)."""
+    import torch
+    osm = _osm()
+    bd, bb, bi = (0.125, 0.25, 0.5), (0.0625, 0.25, 0.375), (0.5, 0.25, 0.75)
+    wt = osm.water_params([(bd, bb, bi), (bb, bd, bi)])
+    J = torch.full((3, blocks, 2048), 0.5, device="cuda")
+    d = torch.full((blocks, 2048), 2.0, device="cuda")
+    J1, d1 = torch.full((3, 1, 5), 0.5, device="cuda"), torch.full((1, 5), 2.0, device="cuda")
+    g_w, _, _ = osm.uw_form_backward([J, J1], [d, d1], wt, [torch.ones_like(J), torch.ones_like(J1)], rows=[0, 1],
+                                     want_image_grads=False)
+    got = g_w.cpu().numpy().astype(np.float64)
+    for row, n, (a, b) in ((0, blocks * 2048, (bd, bb)), (1, 5, (bb, bd))):
+        a, b, i = np.array(a), np.array(b), np.array(bi)
+        want = n * np.concatenate([-0.5 * 2.0 * np.exp(-2.0 * a), i * 2.0 * np.exp(-2.0 * b), 1.0 - np.exp(-2.0 * b)])
+        assert np.all(np.abs(got[row] - want) <= 2e-6 * np.abs(want)), (got[row], want)
