@@ -327,8 +327,10 @@ class RealTimeStep:
                 # the plan's return-gather launch also carries the camera backward
                 "k_ret_uw_bwd": 28 * self.n_returns + 44 * self.npix,
                 "k_uw": 28 * self.npix, "k_uw_bwd": 44 * self.npix,
-                # the plan's binning launch also carries the camera forward
-                "k_bin_uw": 28 * self.n_returns + 28 * self.npix}
+                # the plan's binning and fan launches also carry the camera
+                # forward: 3/8 and 5/8 of an image of this size
+                "k_bin_uw": 28 * self.n_returns + 28 * self.npix * 3 // 8,
+                "k_fan_uw": 4 * npx_fan + 28 * self.npix * 5 // 8}
 
 
 def timed(torch, fn, steps, warmup):

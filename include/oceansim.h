@@ -461,8 +461,8 @@ typedef struct {
 
 /* Casts the ray patterns of n_frames poses (host array, not retained)
  * against the scene, on `stream` (asynchronous; the scene must outlive the
- * enqueued work).  Allocates nothing.  Rays of one beam are cast by
- * neighbouring threads, so the returns come out in beam order.  Errors:
+ * enqueued work).  Allocates nothing.  Ray r of beam b is return
+ * b * n_rays + r: the returns come out in beam order.  Errors:
  * OCEANSIM_E_INVALID_ARG (NULL scene or mat, bad pattern, non-finite pose,
  * a scene of another device), OCEANSIM_E_UNSUPPORTED beyond 2^31 - 1 rays in a
  * frame or for a position beyond 2^40 in magnitude. */
