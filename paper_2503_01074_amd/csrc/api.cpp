@@ -307,8 +307,7 @@ int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_row
         d.wide_cols = d.dphi > 0.09 ? 1 : 0;
         d.scale_phi_f = (float)d.scale_phi;
         d.half_az_f = (float)d.half_az;
-        // FP32 azimuth error, in cells, is below ~3.3e-7 N_phi (see return_bin)
-        d.az_fast = (3.5e-7 * fr.n_azimuth < 1e-3) ? 1 : 0;
+        d.az_edge = 7e-7f * (float)fr.n_azimuth;
         // pointers
         d.x = gcast(fr.x); d.y = gcast(fr.y); d.z = gcast(fr.z);
         d.nx = gcast(fr.nx); d.ny = gcast(fr.ny); d.nz = gcast(fr.nz);

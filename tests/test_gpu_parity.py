@@ -636,3 +636,30 @@ def test_water_gradient_sums_of_any_number_of_partials(blocks):
         a, b, i = np.array(a), np.array(b), np.array(bi)
         want = n * np.concatenate([-0.5 * 2.0 * np.exp(-2.0 * a), i * 2.0 * np.exp(-2.0 * b), 1.0 - np.exp(-2.0 * b)])
         assert np.all(np.abs(got[row] - want) <= 2e-6 * np.abs(want)), (got[row], want)
+
+
+@pytest.mark.parametrize("n_az", [2, 64, 511, 1024, 2047, 2048, 2857, 2858, 4096])
+@pytest.mark.parametrize("fov", [0.05, 2.0943951, 3.1415925])
+def test_returns_at_azimuth_edges(n_az, fov):
+    """Returns from 1e-9 to 1e-2 cells off the azimuth edges, inside and outside
+    the distance below which the FP32 azimuth is redone in FP64 (7e-7 n_az
+    cells): the oracle's bins, exactly."""
+    st = W.Stream(1470, n_az)
+    n = 60000
+    spec = W.SonarSpec(r_min=0.5, r_max=40.0, n_range=16, n_azimuth=n_az, fov_az=fov, fov_el=0.5,
+                       speckle_mode=W.SPECKLE_OFF, alpha=0.02)
+    half, scale = 0.5 * np.float64(np.float32(fov)), n_az / np.float64(np.float32(fov))
+    edge = st.integers(0, n_az, n)
+    off = 10.0 ** st.uniform(-9.0, -2.0, n) * np.where(st.integers(0, 1, n) == 1, 1.0, -1.0)
+    phi, r = (edge + off) / scale - half, st.uniform(0.6, 39.0, n)
+    el = st.uniform(-0.2, 0.2, n)
+    x, y, z = r * np.cos(el) * np.cos(phi), r * np.cos(el) * np.sin(phi), r * np.sin(el)
+    nrm = np.stack([st.uniform(-1.0, 1.0, n) for _ in range(3)])
+    nrm[:, ::7] *= 1e-15   # normals of any length
+    nrm[:, 1::7] *= 1e15
+    nrm[:, 2::97] = 0.0
+    f32 = lambda a: np.asarray(a, np.float32)
+    hits = W.SonarHits(x=f32(x), y=f32(y), z=f32(z), nx=f32(nrm[0]), ny=f32(nrm[1]), nz=f32(nrm[2]),
+                       mat=st.integers(0, 3, n).astype(np.int32), refl=f32([0.2, 0.5, 0.8, 1.0]))
+    got = gpu_forward([W.SonarFrame(spec, hits)], hits.refl, fan=False)[0]
+    check_frame(got, oracle_forward(W.SonarFrame(spec, hits), hits.refl), "n_az %d fov %g" % (n_az, fov), fan=False)
