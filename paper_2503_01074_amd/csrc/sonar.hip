@@ -246,14 +246,16 @@ constexpr int kPairBwdLoads = 4;   // ... of a pair backward tile (more would co
 // thread per round (each pair's segment found from a coarse LDS map of the
 // flat range, built with the prefix, and a short search of the prefix;
 // indices past the end re-read the last pair and are not visited).
-// seg_map: LDS of 2 NT entries.  fn(pair, range):
-// WITH_R loads the pair's range from f.pair_r with the pair (else 0).  pre()
+// seg_map: LDS of 2 NT entries.  fn(pair, range, piled): WITH_R loads the
+// pair's range from f.pair_r with the pair (else 0); piled is std::true_type in
+// the rounds for which piled_up(pair, in) is true, given each lane's first
+// pair of the round (in: not past the end) and uniform in a wave.  pre()
 // runs once, after the first offset loads are issued and before they are
 // used: independent arithmetic placed there overlaps their latency.
 // Contains barriers.
-template <int NT, int LOADS, bool WITH_R, class Fn, class Pre>
+template <int NT, int LOADS, bool WITH_R, class Fn, class Pre, class PiledUp>
 __device__ __forceinline__ void for_tile_pairs(const SonarDev &f, int tile, int *seg_end, int *seg_start, int *wtot,
-                                               unsigned short *seg_map, Fn fn, Pre pre) {
+                                               unsigned short *seg_map, Fn fn, Pre pre, PiledUp piled_up) {
     const int tid = threadIdx.x;
     const int stride = f.n_tiles + 1;
     for (int c0 = 0; c0 < f.n_chunks; c0 += NT) {
@@ -287,9 +289,15 @@ __device__ __forceinline__ void for_tile_pairs(const SonarDev &f, int tile, int 
                 q[u] = gload(f.pairs + idx);
                 rv[u] = WITH_R ? f.pair_r[idx] : 0.0f;
             }
+            auto visit = [&](auto piled) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < LOADS; ++u)
-                if (k0 + u * NT + tid < total) fn(q[u], rv[u]);
+                for (int u = 0; u < LOADS; ++u)
+                    if (k0 + u * NT + tid < total) fn(q[u], rv[u], piled);
+            };
+            if (piled_up(q[0], k0 + tid < total))
+                visit(std::true_type{});
+            else
+                visit(std::false_type{});
         }
         __syncthreads();
     }
@@ -299,11 +307,10 @@ __device__ __forceinline__ void for_tile_pairs(const SonarDev &f, int tile, int 
 // *p += v in LDS.  ds_add_f32 serves its lanes one after the other (193 cycles a
 // wave instruction of the CU's LDS, measured over random addresses, against 6.5
 // of a read or an integer add, and it was 45 % of a tile's time), so the sum is
-// formed in a register and swapped in: 24 cycles over 8192 random addresses, 32
+// formed in a register and swapped in: 28 cycles over 8192 random addresses, 34
 // over 1024.  A lane whose word changed in between tries once more, then falls
-// back to the atomic add, whose cost is 3 cycles a lane: what is left are
-// pile-ups, where retries would only follow one another (all 64 lanes on one
-// address: 257 cycles by ds_add_f32 alone, about 390 this way).
+// back to the atomic add, whose cost is 3 to 4 cycles a lane.  Where many lanes
+// add to one word the swaps only follow one another: for those see piled_up.
 __device__ __forceinline__ void lds_add(float *p, float v) {
     unsigned *u = reinterpret_cast<unsigned *>(p);
     unsigned old = __hip_atomic_load(u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -313,6 +320,29 @@ __device__ __forceinline__ void lds_add(float *p, float v) {
         got = atomicCAS(u, old, __float_as_uint(__uint_as_float(old) + v));
         if (got != old) atomicAdd(p, v);
     }
+}
+
+// Whether a wave's adds to the words b of its lanes (with `in`) are better done
+// by ds_add_f32: the rays of a beam on a wall give returns of one bin, and 64
+// lanes on one word take 504 cycles by swaps against 257, eight words of eight
+// lanes 308 against 249, sixteen of four 184 against 241 (run lengths of lanes;
+// shuffled within 3 % of it).  So: some of three lanes finds its word in eight
+// lanes or more.  Looked up once for a round of a thread's pairs: its few
+// instructions for each pair, or counting the lanes that lost a swap, cost
+// scattered returns 5 to 7 % of the tiles' time, this 1 to 3 %.
+//
+// k_tile alone, us, by ds_add_f32, by swaps, so: 256 frames of 32768 returns
+// scattered over 256 x 256 bins 75, 42.5, 43.4; in one bin 565, 1033, 565.
+// Calls of eight frames of 1024 x 1024 bins, 1024 x 128 rays on a flat wall 130,
+// 187, 130; all at one range (a bin per beam) 1468, 2707, 1470.
+__device__ __forceinline__ bool piled_up(unsigned b, bool in) {
+    int most = 0;
+#pragma unroll
+    for (int at = kWave / 4; at < kWave; at += kWave / 4) {
+        const unsigned word = (unsigned)__builtin_amdgcn_readlane((int)b, at);
+        most = max(most, (int)__popcll(__ballot(in && b == word)));
+    }
+    return most >= 8;
 }
 
 // Wave-level stream compaction: every wave walks its share of [0, n), queues
@@ -468,14 +498,18 @@ __device__ __forceinline__ void tile_fwd_block(const Src &src, const oceansim_so
     float cemax = 0.0f;
     for_tile_pairs<NT, kTileLoads, false>(
         f, tile, seg_end, seg_start, wtot, queues,   // the queues serve as the segment map until the compaction
-        [&](uint2 q, float) __attribute__((always_inline)) {
+        [&](uint2 q, float, auto piled) __attribute__((always_inline)) {
             const uint32_t lb = matp ? (q.x & 0xffffu) : q.x;
             if (lb >= (uint32_t)nbins) return;
             const float I = matp ? refl_s[q.x >> 16] * __uint_as_float(q.y) : __uint_as_float(q.y);
             cemax = fmaxf(cemax, __builtin_fabsf(__uint_as_float(q.y)));
-            lds_add(&acc[lb], I);
+            if constexpr (decltype(piled)::value)
+                atomicAdd(&acc[lb], I);
+            else
+                lds_add(&acc[lb], I);
         },
-        []() {});
+        []() {},
+        [&](uint2 q, bool in) __attribute__((always_inline)) { return piled_up(matp ? (q.x & 0xffffu) : q.x, in); });
     if (f.tile_cemax) {
         __shared__ unsigned s_cemax;
         if (tid == 0) s_cemax = 0u;
@@ -1617,7 +1651,7 @@ __device__ __forceinline__ void pair_bwd_block(const Src &src, const oceansim_so
     bool bad_a = !__builtin_isfinite(B_alpha), bad_g = !__builtin_isfinite(B_gain);
     bool bad_s = paper && !__builtin_isfinite(B_ssm);
     const double neg_kappa = -f.kappa;
-    for_tile_pairs<NT, kPairBwdLoads, true>(f, tile, seg_end, seg_start, wtot, seg_map, [&](uint2 pq, float r) __attribute__((always_inline)) {
+    for_tile_pairs<NT, kPairBwdLoads, true>(f, tile, seg_end, seg_start, wtot, seg_map, [&](uint2 pq, float r, auto) __attribute__((always_inline)) {
         const uint32_t lb = pq.x & 0xffffu;
         const int m = (int)(pq.x >> 16);
         if (lb >= (uint32_t)(b_hi - b_lo) || m >= n_mat) return;
@@ -1647,7 +1681,7 @@ __device__ __forceinline__ void pair_bwd_block(const Src &src, const oceansim_so
         }
         if (__builtin_isfinite(xa)) a_alpha += scale_round(xa, s_alpha); else bad_a = true;
         if (__builtin_isfinite(xg)) a_gain += scale_round(xg, s_gain); else bad_g = true;
-    }, []() {});
+    }, []() {}, [](uint2, bool) { return false; });
 
     // 4. workgroup sums (integers: any order; doubles: a fixed order)
     long long lv[3] = {a_alpha, a_gain, a_ssm};
