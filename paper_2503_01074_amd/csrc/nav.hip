@@ -9,8 +9,10 @@
 //           the ticks' ping periods in parallel, the measurement schedule
 //           (which carries the time of the last measurement from tick to
 //           tick) by one wave, the due measurements from a compacted list.
-//           Inputs are tick-major ([tick][instance]), so the loads of a tick
-//           are coalesced across the lanes of a wave.
+//   k_dvl_walk  one thread per instance, walking its ticks: few ticks or very
+//           many instances (dvl_walks).
+// Inputs are tick-major ([tick][instance]), so the loads of a tick are
+// coalesced across the lanes of a wave.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -240,6 +242,83 @@ __global__ __launch_bounds__(kDvlThreads, 4) void k_dvl(gptr<const double> t, gp
     write_slab(last, b3 == 0 ? 2 : b3 - 1, wave, kDvlWaves);
 }
 
+// One thread per instance, walking its ticks.  Where there are waves enough to
+// hide a tick's loads it is bound by HBM (8 ticks x 1048576 instances: 70 us,
+// 5.3 TB/s), or by the solutions' VALU work where every tick is due.
+__global__ __launch_bounds__(kNavThreads) void k_dvl_walk(gptr<const double> t, gptr<const float4> ranges,
+                                                          gptr<const float> vel, int n_ticks, int n_inst, DvlDev p,
+                                                          gptr<float> vout, gptr<int> status) {
+    const int n = blockIdx.x * kNavThreads + threadIdx.x;
+    if (n >= n_inst) return;
+    double t_last = 0.0;
+    bool have_last = false;
+    // the next tick's inputs are loaded while this tick is processed (past
+    // the last tick the loads re-read it)
+    float4 r4n = gload((gptr<const float4>)(ranges + n));
+    float vn0 = vel[3LL * n], vn1 = vel[3LL * n + 1], vn2 = vel[3LL * n + 2];
+    for (int k = 0; k < n_ticks; ++k) {
+        const long long row = (long long)k * n_inst + n;
+        const float r[4] = {r4n.x, r4n.y, r4n.z, r4n.w};
+        const double v0 = vn0, v1 = vn1, v2 = vn2;
+        {
+            const long long nrow = (long long)(k + 1 < n_ticks ? k + 1 : k) * n_inst + n;
+            r4n = gload((gptr<const float4>)(ranges + nrow));
+            vn0 = vel[3 * nrow];
+            vn1 = vel[3 * nrow + 1];
+            vn2 = vel[3 * nrow + 2];
+        }
+        unsigned ok = 0u;
+        double r_ref = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const double ri = (double)r[i];
+            if (__builtin_isfinite(ri) && ri >= p.range_min && ri <= p.range_max) {
+                ok |= 1u << i;
+                r_ref = ri > r_ref ? ri : r_ref;
+            }
+        }
+        if (ok == 0u) r_ref = p.range_max;
+        double period = p.pings_per_output * 2.0 * r_ref / p.sound_speed;
+        period = period < p.period_min ? p.period_min : period;
+        const double tk = t[k];
+        const bool due = !have_last || (tk - t_last >= period);
+        float o[3] = {__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+        int s = 0;
+        if (due) {
+            have_last = true;
+            t_last = tk;
+            s = 2;
+            if (__popc(ok) >= p.min_beams) {
+                s = 1;
+                dvl_solve(p, k, n, ok, v0, v1, v2, o);
+            }
+        }
+        const gptr<float> vo = vout + 3 * row;
+        vo[0] = o[0];
+        vo[1] = o[1];
+        vo[2] = o[2];
+        status[row] = s;
+    }
+}
+
+// Which calls walk.  k_dvl reduces slabs of 32 ticks whatever their number and
+// gives up one wave of eight to the schedule; walking needs instances to fill
+// the chip.  Walked / k_dvl, us, with about one tick in fourteen due (with
+// every tick due):
+//   49152 instances,  8 ticks  10 / 11 (14 / 13)     24 ticks   32 / 20 (37 / 26)
+//   65536             8        10 / 13 (14 / 16)     24         32 / 24 (37 / 33)
+//   98304            16        25 / 31 (34 / 35)     24         39 / 34 (49 / 48)
+//   131072           32        54 / 51 (64 / 78)     64        121 / 92 (133 / 144)     128  246 / 155 (261 / 260)
+//   262144           32        89 / 107 (111 / 161)  64        182 / 170 (217 / 275)    256  758 / 548 (842 / 956)
+//   1048576           1        15 / 143 (14 / 143)    8         70 / 184 (102 / 237)     64  629 / 617 (797 / 1049)
+// How many ticks are due is in the data, so the line lies where k_dvl is the
+// faster one either way.
+bool dvl_walks(int n_ticks, int n_inst) {
+    if (n_inst >= 163840) return true;
+    if (n_inst >= 114688) return n_ticks <= 64;
+    return n_inst >= 49152 && n_ticks <= n_inst / 4096 - 4;
+}
+
 bool aligned_to(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 }  // namespace
@@ -313,10 +392,12 @@ int oceansim_dvl(const double *t_dev, const float *ranges_dev, const float *velo
     p.seed_lo = q.seed_lo;
     p.seed_hi = q.seed_hi;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int blocks = (int)(((long long)n_inst + kDvlInst - 1) / kDvlInst);
-    OSIM_LAUNCH("k_dvl", k_dvl, dim3(blocks), dim3(kDvlThreads), 0, st, gcast(t_dev),
-                gcast(reinterpret_cast<const float4 *>(ranges_dev)), gcast(velocity_dev), (int)n_ticks, (int)n_inst,
-                p, gcast(velocity_out_dev), gcast(status_dev));
+    const bool walk = dvl_walks(n_ticks, n_inst);
+    const int per_block = walk ? kNavThreads : kDvlInst;
+    const int blocks = (int)(((long long)n_inst + per_block - 1) / per_block);
+    OSIM_LAUNCH("k_dvl", walk ? k_dvl_walk : k_dvl, dim3(blocks), dim3(walk ? kNavThreads : kDvlThreads), 0, st,
+                gcast(t_dev), gcast(reinterpret_cast<const float4 *>(ranges_dev)), gcast(velocity_dev), (int)n_ticks,
+                (int)n_inst, p, gcast(velocity_out_dev), gcast(status_dev));
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? ok() : hip_fail(e, "dvl launch");
 }

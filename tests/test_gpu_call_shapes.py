@@ -60,3 +60,36 @@ def test_returns_in_one_bin():
     t = {k: _kernel_us(lambda: osm.render_sonar([g] * frames, [h] * frames, params, refl), "k_tile")
          for k, h in (("piled", piled), ("spread", spread))}
     assert t["piled"] < 18.0 * t["spread"], t
+
+
+def _wall_us(fn):
+    """Best of five mean times of 20 calls."""
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    fn()
+    best = float("inf")
+    for _ in range(5):
+        a.record()
+        for _ in range(20):
+            fn()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / 20 * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("ticks, vehicles", [(1, 1 << 20), (8, 1 << 20), (16, 1 << 18)])
+def test_dvl_of_few_ticks(ticks, vehicles):
+    """A few ticks of very many vehicles against a copy of the same bytes (or
+    12 us): 1 to 1.5 times its time; a workgroup's slab of 32 ticks for each 64
+    vehicles takes 2.7 to 12 times."""
+    import paper_2503_01074_amd as osm
+    _say("DVL %d x %d" % (ticks, vehicles))
+    gen = torch.Generator(device="cuda").manual_seed(ticks)
+    t = torch.arange(ticks, device="cuda", dtype=torch.float64) * 0.02
+    r = torch.rand(ticks, vehicles, 4, generator=gen, device="cuda") * 80.0 + 2.0
+    v = torch.randn(ticks, vehicles, 3, generator=gen, device="cuda")
+    src = torch.zeros(ticks * vehicles * 22, dtype=torch.uint8, device="cuda")
+    dst = torch.empty_like(src)
+    copy = _wall_us(lambda: dst.copy_(src))
+    dvl = _wall_us(lambda: osm.dvl(t, r, v, sigma_v=0.01, seed=(1, 2)))
+    assert dvl < 2.0 * max(copy, 12.0), (dvl, copy)

@@ -93,3 +93,24 @@ def test_dvl_slabs_and_instance_groups(T, N, dt):
     assert np.all(np.isnan(vo[~good]))
     if good.any():
         assert_image_close(vo[good], want_v[good], "dvl velocity")
+
+
+@pytest.mark.parametrize("T, N", [(8, 49151), (8, 49152), (9, 49152), (1, 163839), (3, 163841)])
+def test_dvl_few_ticks_of_many_instances(T, N):
+    """Sizes on both sides of the lines between workgroups of 64 instances and
+    one thread per instance (the last one in a partial workgroup)."""
+    import torch
+    import paper_2503_01074_amd as osm
+    rs = np.random.default_rng(T + N)
+    t = np.cumsum(rs.uniform(0.05, 0.3, T))
+    _, ranges, vel = _dvl_case(T, N, T * N)
+    cfg = DvlConfig(sigma_v=0.02, pings_per_output=1.0, seed_lo=5, seed_hi=6)
+    vo, st = osm.dvl(torch.as_tensor(t).cuda(), torch.as_tensor(ranges).cuda(), torch.as_tensor(vel).cuda(),
+                     sigma_v=0.02, pings_per_output=1.0, seed=(5, 6))
+    torch.cuda.synchronize()
+    want_v, want_s = oracle.dvl(t, ranges, vel, cfg)
+    np.testing.assert_array_equal(st.cpu().numpy(), want_s)
+    vo = vo.cpu().numpy()
+    good = want_s == 1
+    assert good.any() and np.all(np.isnan(vo[~good]))
+    assert_image_close(vo[good], want_v[good], "dvl velocity")
