@@ -216,6 +216,8 @@ int build_bvh(const float *vertices, long long n_vertices, const int32_t *triang
     B.prims.reserve((size_t)n_triangles);
     std::vector<long long> kept;
     kept.reserve((size_t)n_triangles);
+    std::vector<double> area;
+    area.reserve((size_t)n_triangles);
     for (long long f = 0; f < n_triangles; ++f) {
         double v[3][3];
         for (int j = 0; j < 3; ++j) {
@@ -244,6 +246,7 @@ int build_bvh(const float *vertices, long long n_vertices, const int32_t *triang
         for (int a = 0; a < 3; ++a) p.c[a] = 0.5 * (p.box.lo[a] + p.box.hi[a]);
         p.tri = (int)kept.size();
         kept.push_back(f);
+        area.push_back(0.5 * nl);
         B.prims.push_back(p);
     }
     const long long n_kept = (long long)kept.size();
@@ -255,7 +258,15 @@ int build_bvh(const float *vertices, long long n_vertices, const int32_t *triang
     }
     B.nodes.reserve((size_t)std::max(1LL, n_kept / 2));
     B.order.reserve((size_t)n_kept);
-    const double root_area = B.bounds(0, (int)n_kept).area();
+    const Box box = B.bounds(0, (int)n_kept);
+    const double root_area = box.area();
+    for (int a = 0; a < 3; ++a) {
+        out.lo[a] = box.lo[a];
+        out.hi[a] = box.hi[a];
+    }
+    const auto quarter = area.begin() + (area.size() - 1) / 4;
+    std::nth_element(area.begin(), quarter, area.end());
+    out.tri_area = *quarter;
     out.root = B.build(0, (int)n_kept, 0);
     if (B.depth > kBvhMaxDepth) return fail(OCEANSIM_E_UNSUPPORTED, "hierarchy deeper than %d levels", kBvhMaxDepth);
     out.empty = false;

@@ -3,14 +3,16 @@
 // hits of a beam x elevation ray pattern against a triangle mesh in a binary
 // bounding-volume hierarchy (built on the host, bvh.cpp).
 //
-//   k_raycast_packet  (patterns of fine angular steps) a wave traverses the
+//   k_raycast_packet  (patterns of angular steps that are fine against the
+//              scene's triangles) a wave traverses the
 //              hierarchy once for an 8 x 8 patch of beams and rays: node and
 //              triangle records come through scalar loads, each lane tests the
 //              boxes for its own ray, and the wave's stack holds references
 //              with the mask of the lanes that met the box.
-//   k_raycast  (coarse patterns) each lane traverses for itself, with a stack
+//   k_raycast  (the others) each lane traverses for itself, with a stack
 //              of its own in LDS (thread-minor, so a wave's stack accesses are
-//              conflict-free).
+//              conflict-free); over dense scenes a wave takes the rays of one
+//              beam.
 //
 // Both are ordered: an inner node holds both child boxes (one 64-byte record),
 // the nearer child is taken first and the other deferred; leaves hold at most
@@ -40,6 +42,7 @@ struct oceansim_scene {
     osim::BvhTri *tris = nullptr;
     int root = 0;
     int empty = 1;
+    double lo[3], hi[3], tri_area;   // see BvhBuild
     oceansim_scene_info info{};
 };
 
@@ -47,6 +50,8 @@ namespace osim {
 namespace {
 
 constexpr int kRayThreads = 256;
+constexpr int kRayLineThreads = 128;   // of a workgroup whose waves take lines of rays (see ray_shape)
+constexpr int kRayXcdRun = 16;         // consecutive tiles one XCD takes
 constexpr int kRayFramesPerLaunch = 16;
 constexpr float kSlabWiden = 1.00000036f;   // 1 + 2 gamma_3, gamma_n = n eps / (1 - n eps), eps = 2^-24
 
@@ -75,22 +80,26 @@ __device__ __forceinline__ float4 ld4(gptr<const float4> p) { return gload(p); }
 template <class T>
 using cptr = const __attribute__((address_space(4))) T *;
 
-// A workgroup casts a tile of 256 rays: 2^br neighbouring rays of 256 / 2^br
-// neighbouring beams, each wave a patch of 2^wr rays of 2^(6 - wr) beams,
-// about as wide as it is high (ray_shape), so that its rays meet nearly the
-// same nodes: on a seabed, 64 rays of one beam step through a third more.
-// The waves of a tile lie side by side along the rays up to 32 of them, so
-// that a beam's rays fill whole cache lines of the output.
+// A workgroup of NT threads casts a tile of NT rays: 2^br neighbouring rays of
+// NT / 2^br neighbouring beams, each wave a patch of 2^wr rays of 2^(6 - wr)
+// beams (ray_shape).  The waves of a tile lie side by side along the rays up
+// to 32 of them, so that a beam's rays fill whole cache lines of the output.
+// Neighbouring tiles meet the same nodes and triangles, so runs of 16 go to one
+// XCD, rotated (a beam's tiles divide a round, and its elevations differ in
+// cost): 8 x (2048 x 1024) rays on a seabed of 130,242 triangles 517 -> 411 us by
+// one traversal per wave, on one of 2 M triangles 1608 -> 1240 us by lanes.
 struct RayTile {
     int beams, rays;          // tile size
     int b0, r0;               // its first beam and ray
     int b, r;                 // this thread's, within the tile
 };
-__device__ __forceinline__ RayTile ray_tile(const RayFrameDev &f, int tile, int tid) {
+template <int NT>
+__device__ __forceinline__ RayTile ray_tile(const RayFrameDev &f, int block, int tid) {
     RayTile t;
+    const int tile = xcd_rotated_id<kRayXcdRun>(block, f.n_tiles);
     const int br = f.br_log2, wr = f.wr_log2;
     t.rays = 1 << br;
-    t.beams = kRayThreads >> br;
+    t.beams = NT >> br;
     const int tb = tile / f.tiles_r;
     t.b0 = tb * t.beams;
     t.r0 = (tile - tb * f.tiles_r) << br;
@@ -119,8 +128,9 @@ struct Ray {
 
 // The rays of the tile: one sine and cosine per beam and per ray of the tile,
 // shared through LDS (trig holds the beams', then the rays').  Contains a barrier.
+template <int NT>
 __device__ __forceinline__ Ray ray_of(const RayFrameDev &f, const RayTile &t, int tid, float2 *trig) {
-    for (int k = tid; k < t.beams + t.rays; k += kRayThreads) {
+    for (int k = tid; k < t.beams + t.rays; k += NT) {
         const bool beam = k < t.beams;
         const float a = beam ? __builtin_fmaf((float)(t.b0 + k) + 0.5f, f.daz, f.az0)
                              : __builtin_fmaf((float)(t.r0 + k - t.beams) + 0.5f, f.del, f.el0);
@@ -246,15 +256,16 @@ __device__ __forceinline__ void write_return(const RayFrameDev &f, const Ray &q,
     f.mat[k] = m;
 }
 
-__global__ __launch_bounds__(kRayThreads) void k_raycast(RayGroup g, gptr<const float4> nodes, gptr<const float4> tris,
-                                                         int root, int empty) {
-    extern __shared__ int stk[];   // [depth of the scene][kRayThreads]: a deferred child per level at most
-    __shared__ float2 trig[kRayThreads + 1];
+template <int NT>
+__global__ __launch_bounds__(NT) void k_raycast(RayGroup g, gptr<const float4> nodes, gptr<const float4> tris,
+                                                int root, int empty) {
+    extern __shared__ int stk[];   // [depth of the scene][NT]: a deferred child per level at most
+    __shared__ float2 trig[NT + 1];
     const RayFrameDev &f = g.f[blockIdx.y];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= f.n_tiles) return;
-    const RayTile tl = ray_tile(f, blockIdx.x, tid);
-    const Ray q = ray_of(f, tl, tid, trig);
+    const RayTile tl = ray_tile<NT>(f, blockIdx.x, tid);
+    const Ray q = ray_of<NT>(f, tl, tid, trig);
     const int b = tl.b0 + tl.b, r = tl.r0 + tl.r;
     if (b >= f.nb || r >= f.nr) return;
     const float o0 = f.o[0], o1 = f.o[1], o2 = f.o[2];
@@ -274,7 +285,7 @@ __global__ __launch_bounds__(kRayThreads) void k_raycast(RayGroup g, gptr<const 
                 if (h0 && h1) {
                     const bool swap = t1 < t0;
                     ref = swap ? rr.y : rr.x;
-                    stk[sp * kRayThreads + tid] = swap ? rr.x : rr.y;
+                    stk[sp * NT + tid] = swap ? rr.x : rr.y;
                     ++sp;
                     continue;
                 }
@@ -298,7 +309,7 @@ __global__ __launch_bounds__(kRayThreads) void k_raycast(RayGroup g, gptr<const 
             }
             if (sp == 0) break;
             --sp;
-            ref = stk[sp * kRayThreads + tid];
+            ref = stk[sp * NT + tid];
         }
     }
     write_return(f, q, tris, b * f.nr + r, hit, tbest);
@@ -418,8 +429,8 @@ __global__ __launch_bounds__(kRayThreads) void k_raycast_packet(RayGroup g, gptr
     const RayFrameDev &f = g.f[blockIdx.y];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= f.n_tiles) return;
-    const RayTile tl = ray_tile(f, blockIdx.x, tid);
-    const Ray q = ray_of(f, tl, tid, trig);
+    const RayTile tl = ray_tile<kRayThreads>(f, blockIdx.x, tid);
+    const Ray q = ray_of<kRayThreads>(f, tl, tid, trig);
     const int b = tl.b0 + tl.b, r = tl.r0 + tl.r;
     const bool live = b < f.nb && r < f.nr;
     const unsigned long long live_m = __ballot(live);
@@ -457,32 +468,67 @@ int ceil_log2(int v) {
     return e;
 }
 
-// The wave's patch: 2^wr rays of 2^(6 - wr) beams, its angular height about
-// half its width (elevation steps are stretched on the ground by the grazing
-// incidence), no more rays or beams than the pattern has.  The tile: waves
-// along the rays up to 32 rays, the rest along the beams, again within the
-// pattern.
-void ray_shape(int n_beams, int n_rays, float daz, float del, int &wr, int &br) {
+// The wave's patch: 2^wr rays of 2^(6 - wr) beams, no more rays or beams than
+// the pattern has.  Its angular height is about half its width (elevation
+// steps are stretched on the ground by the grazing incidence), so that its rays
+// meet nearly the same nodes: on a seabed, 64 rays of one beam step through a
+// third more.  With `line` it is such a line of 64 rays all the same: over
+// triangles smaller than the rays' spacing nothing is shared, and a square
+// patch only puts the costly rays into few waves.
+// The tile of 2^threads_log2 rays: waves along the rays up to 32 rays, the rest
+// along the beams, again within the pattern.
+void ray_shape(int n_beams, int n_rays, float daz, float del, bool line, int threads_log2, int &wr, int &br) {
     const int nb2 = ceil_log2(n_beams), nr2 = ceil_log2(n_rays);
-    wr = 3;
-    if (daz > 0.0f && del > 0.0f) wr = (int)std::lround(0.5 * (5.0 + std::log2((double)daz / (double)del)));
+    wr = line ? 6 : 3;
+    if (!line && daz > 0.0f && del > 0.0f)
+        wr = (int)std::lround(0.5 * (5.0 + std::log2((double)daz / (double)del)));
     wr = std::min(std::max(wr, 0), 6);
     wr = std::max(std::min(wr, nr2), std::min(6, 6 - nb2));   // few rays, then few beams
     br = wr;
-    while (br < wr + 2 && br < nr2 && (br < 5 || 8 - br > nb2)) ++br;
+    while (br < wr + threads_log2 - 6 && br < nr2 && (br < 5 || threads_log2 - br > nb2)) ++br;
 }
 
-// One traversal per wave pays where its patch is narrow (64 daz del, in
-// steradians, within 5e-4) and the launch fills the chip (2^18 rays: 4 waves a
-// SIMD): its steps are cheaper but more, since a wave visits what any of its
-// rays meets, and in a small launch only their number counts.  Seabed of
-// 130,242 triangles, one traversal per wave against one per lane: 9 x (2048 x
-// 256) rays 162 / 304 us, 1 x (2048 x 256) 34 / 49, 9 x (2048 x 64) 86 / 111,
-// 4 x (1024 x 128) 54 / 61; but 9 x (1024 x 64), 7.6e-4 sr, 78 / 69, and 1 x
-// (1024 x 128) 40 / 33.  kPacketNodes: its 32-bit offsets into the node and
-// triangle arrays.
+// Triangles in a wave's patch, roughly: its footprint half way to what the
+// cast can reach (or where the scene begins), across the ray, over the area
+// that a quarter of the triangles do not exceed: rather too many than too few
+// where a dense object stands on a coarse floor.
+double patch_triangles(const oceansim_scene &s, const oceansim_ray_frame &q, float daz, float del) {
+    if (s.empty) return 0.0;
+    double near2 = 0.0, far2 = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        const double below = s.lo[a] - (double)q.pos[a], above = (double)q.pos[a] - s.hi[a];
+        const double n = std::max({below, above, 0.0});
+        const double f = std::max(std::fabs(below), std::fabs(above));
+        near2 += n * n;
+        far2 += f * f;
+    }
+    const double r = std::max(std::sqrt(near2), 0.5 * std::min((double)q.t_max, std::sqrt(far2)));
+    return (double)kWave * daz * del * r * r / s.tri_area;
+}
+
+// Which traversal.  One per wave pays where its patch is narrow (64 daz del, in
+// steradians, within 5e-4), holds few triangles and the launch fills the
+// chip (2^18 rays: 4 waves a SIMD): its steps are cheaper but more, since a wave
+// visits what any of its rays meets, and in a small launch only their number
+// counts.  Seabed of 130,242 triangles, t_max 50, one traversal per wave
+// against one per lane: 9 x (2048 x 256) rays 162 / 304 us, 1 x (2048 x 256)
+// 34 / 49, 9 x (2048 x 64) 86 / 111, 4 x (1024 x 128) 54 / 61; but 9 x (1024 x 64),
+// 7.6e-4 sr, 78 / 69, and 1 x (1024 x 128) 40 / 33.
+// Triangles in a patch, per wave / per lane, over seabeds of 1,250 to 8 M
+// triangles: 0.7 (1 x (2048 x 256) rays) 38 / 52 us, 0.75 (8 x (2048 x 1024)) 1108 /
+// 1609, 1.5 (1 x (512 x 512)) 37 / 32, 2.0 (9 x (2048 x 256)) 344 / 430, 2.2 (16 x (512
+// x 512)) 124 / 130, 3 (4 x (1024 x 128)) 103 / 67, 12 (the same) 228 / 82; over a
+// hull of 320,000 triangles on a floor of two 558 / 223.  Inside a closed tank,
+// where no ray grazes a wall, one per wave would pay up to 20 of them and more
+// (165 / 298 us at 5): the scene's numbers do not tell it from the others.
+// Lanes take lines instead of square patches from six triangles on: square / line
+// over the hull 223 / 146 us, before waves took patches 158, and 9 x (1024 x 64)
+// rays on 2 M triangles 222 / 178 (182), though 4 x (1024 x 128) there 82 / 101 (98).
+// kPacketNodes: the packet's 32-bit offsets into the node and triangle arrays.
 constexpr double kPacketSteradians = 5e-4;
-constexpr long long kPacketRays = 1LL << 18;
+constexpr double kPacketTriangles = 1.25, kPacketTrianglesLarge = 2.5;   // below and from kPacketLargeRays on
+constexpr double kSquareTriangles = 6.0;
+constexpr long long kPacketRays = 1LL << 18, kPacketLargeRays = 1LL << 20;
 constexpr long long kPacketNodes = 1LL << 26;
 
 bool finite_all(const float *v, int n) {
@@ -519,6 +565,11 @@ int oceansim_scene_create(const float *vertices, int64_t n_vertices, const int32
     s->root = B.root;
     s->empty = B.empty ? 1 : 0;
     s->info = B.info;
+    s->tri_area = B.tri_area;
+    for (int a = 0; a < 3; ++a) {
+        s->lo[a] = B.lo[a];
+        s->hi[a] = B.hi[a];
+    }
     if (e == hipSuccess && !B.empty) {
         e = hipMalloc((void **)&s->nodes, sizeof(BvhNode) * (size_t)std::max(1LL, B.n_nodes));
         if (e == hipSuccess) e = hipMalloc((void **)&s->tris, sizeof(BvhTri) * (size_t)B.n_tris);
@@ -582,7 +633,9 @@ int oceansim_raycast(const oceansim_scene *scene, const oceansim_ray_frame *fram
         return fail(OCEANSIM_E_INVALID_ARG, "the scene lives on device %d, the current device is %d", scene->device,
                     dev);
     std::vector<RayFrameDev> fd;
+    std::vector<double> dense;   // triangles in a patch
     fd.reserve((size_t)n_frames);
+    dense.reserve((size_t)n_frames);
     for (int i = 0; i < n_frames; ++i) {
         const oceansim_ray_frame &q = frames[i];
         if (q.n_beams < 0 || q.n_rays < 0) return fail(OCEANSIM_E_SHAPE, "frame %d: negative beam or ray count", i);
@@ -614,11 +667,6 @@ int oceansim_raycast(const oceansim_scene *scene, const oceansim_ray_frame *fram
         d.t_max = q.t_max;
         d.nb = q.n_beams;
         d.nr = q.n_rays;
-        ray_shape(q.n_beams, q.n_rays, d.daz, d.del, d.wr_log2, d.br_log2);
-        const long long tr = ((long long)q.n_rays + (1 << d.br_log2) - 1) >> d.br_log2;
-        const long long tb = ((long long)q.n_beams + (kRayThreads >> d.br_log2) - 1) / (kRayThreads >> d.br_log2);
-        d.tiles_r = (int)tr;
-        d.n_tiles = (int)(tr * tb);   // padded to less than twice the rays where these near 2^31: a valid grid
         d.x = gcast(q.x);
         d.y = gcast(q.y);
         d.z = gcast(q.z);
@@ -627,6 +675,7 @@ int oceansim_raycast(const oceansim_scene *scene, const oceansim_ray_frame *fram
         d.nz = gcast(q.nz);
         d.mat = gcast(q.mat);
         fd.push_back(d);
+        dense.push_back(patch_triangles(*scene, q, d.daz, d.del));
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     const gptr<const float4> nodes = gcast(reinterpret_cast<const float4 *>(scene->nodes));
@@ -635,22 +684,40 @@ int oceansim_raycast(const oceansim_scene *scene, const oceansim_ray_frame *fram
         RayGroup grp;
         std::memset(&grp, 0, sizeof grp);
         const int cnt = (int)std::min<size_t>(kRayFramesPerLaunch, fd.size() - g0);
-        int tiles = 0;
         long long rays = 0;
         bool packet = scene->info.n_triangles < kPacketNodes;   // more triangles than nodes
+        double most = 0.0;   // triangles in a patch
         for (int j = 0; j < cnt; ++j) {
-            const RayFrameDev &d = grp.f[j] = fd[g0 + j];
-            tiles = std::max(tiles, d.n_tiles);
+            const RayFrameDev &d = fd[g0 + j];
             rays += (long long)d.nb * d.nr;
-            packet = packet && 64.0 * d.daz * d.del <= kPacketSteradians;
+            packet = packet && (double)kWave * d.daz * d.del <= kPacketSteradians;
+            most = std::max(most, dense[g0 + j]);
         }
-        packet = packet && rays >= kPacketRays;
+        packet = packet && rays >= kPacketRays &&
+                 most <= (rays >= kPacketLargeRays ? kPacketTrianglesLarge : kPacketTriangles);
+        const bool line = most > kSquareTriangles;
+        const int nt = line ? kRayLineThreads : kRayThreads;
+        int tiles = 0;
+        for (int j = 0; j < cnt; ++j) {
+            RayFrameDev &d = grp.f[j] = fd[g0 + j];
+            ray_shape(d.nb, d.nr, d.daz, d.del, line, ceil_log2(nt), d.wr_log2, d.br_log2);
+            const int beams = nt >> d.br_log2;
+            const long long tr = ((long long)d.nr + (1 << d.br_log2) - 1) >> d.br_log2;
+            const long long tb = ((long long)d.nb + beams - 1) / beams;
+            d.tiles_r = (int)tr;
+            d.n_tiles = (int)(tr * tb);   // padded to less than twice the rays where these near 2^31: a valid grid
+            tiles = std::max(tiles, d.n_tiles);
+        }
+        const dim3 grid((unsigned)tiles, (unsigned)cnt);
+        const size_t stack = (size_t)std::max(1, scene->info.depth) * nt * sizeof(int);
         if (packet)
-            OSIM_LAUNCH("k_raycast", k_raycast_packet, dim3((unsigned)tiles, (unsigned)cnt), dim3(kRayThreads), 0, st,
-                        grp, nodes, tris, scene->root, scene->empty);
+            OSIM_LAUNCH("k_raycast", k_raycast_packet, grid, dim3(kRayThreads), 0, st, grp, nodes, tris, scene->root,
+                        scene->empty);
+        else if (line)
+            OSIM_LAUNCH("k_raycast", k_raycast<kRayLineThreads>, grid, dim3(kRayLineThreads), stack, st, grp, nodes,
+                        tris, scene->root, scene->empty);
         else
-            OSIM_LAUNCH("k_raycast", k_raycast, dim3((unsigned)tiles, (unsigned)cnt), dim3(kRayThreads),
-                        (size_t)std::max(1, scene->info.depth) * kRayThreads * sizeof(int), st, grp, nodes, tris,
+            OSIM_LAUNCH("k_raycast", k_raycast<kRayThreads>, grid, dim3(kRayThreads), stack, st, grp, nodes, tris,
                         scene->root, scene->empty);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "ray-cast launch");

@@ -56,6 +56,8 @@ struct BvhBuild {
     long long n_nodes = 0;
     BvhTri *tris = nullptr;
     long long n_tris = 0;
+    double lo[3] = {}, hi[3] = {};   // box of the kept triangles
+    double tri_area = 0.0;           // a quarter of them are no larger than this
     oceansim_scene_info info{};
 };
 

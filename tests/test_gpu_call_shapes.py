@@ -93,3 +93,37 @@ def test_dvl_of_few_ticks(ticks, vehicles):
     copy = _wall_us(lambda: dst.copy_(src))
     dvl = _wall_us(lambda: osm.dvl(t, r, v, sigma_v=0.01, seed=(1, 2)))
     assert dvl < 2.0 * max(copy, 12.0), (dvl, copy)
+
+
+def _hull_over_floor(n=400, radius=3.0):
+    """A floor of two triangles and a sphere of 2 n (n - 1) over it."""
+    u, w = np.meshgrid(np.linspace(0, 2 * np.pi, n, endpoint=False), np.linspace(0.02, np.pi - 0.02, n), indexing="ij")
+    v = np.stack([6.0 + radius * np.sin(w) * np.cos(u), radius * np.sin(w) * np.sin(u),
+                  -14.0 + radius * np.cos(w)], -1).reshape(-1, 3)
+    i = np.arange(n * n).reshape(n, n)
+    a, b, c, d = i[:, :-1], np.roll(i, -1, 0)[:, :-1], np.roll(i, -1, 0)[:, 1:], i[:, 1:]
+    t = np.concatenate([np.stack([a, b, c], -1).reshape(-1, 3), np.stack([a, c, d], -1).reshape(-1, 3)]) + 4
+    floor = np.array([[-2e3, -2e3, -20], [2e3, -2e3, -20], [2e3, 2e3, -20], [-2e3, 2e3, -20]])
+    v = np.concatenate([floor, v]).astype(np.float32)
+    t = np.concatenate([[[0, 1, 2], [0, 2, 3]], t]).astype(np.int32)
+    return v, t, (np.arange(len(t)) % 61).astype(np.int32)
+
+
+def test_cast_over_a_dense_object():
+    """Four poses in one launch against four launches of one, over an object
+    whose triangles are far smaller than the rays' spacing: a third of
+    their time; by one traversal for all rays of a wave as long or longer."""
+    import paper_2503_01074_amd as osm
+    _say("cast over a dense object")
+    scene = osm.Scene(*_hull_over_floor())
+    pose = (np.array([-24.0, 0.0, -13.0], np.float32), np.eye(3, dtype=np.float32))
+    args = (1024, 128, float(np.float32(2.2)), float(np.float32(0.4)), 50.0)
+    one = osm.raycast(scene, [pose], *args)
+    four = osm.raycast(scene, [pose] * 4, *args)
+    for h in four:
+        assert torch.equal(h.mat, one[0].mat) and torch.equal(h.x, one[0].x)
+    assert (one[0].mat >= 0).any()
+    other = 4 * _wall_us(lambda: osm.raycast(scene, [pose], *args, out=one))
+    cast = _wall_us(lambda: osm.raycast(scene, [pose] * 4, *args, out=four))
+    assert cast < 0.6 * other, (cast, other)
+    scene.close()

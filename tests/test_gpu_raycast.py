@@ -278,3 +278,27 @@ def test_shared_traversal_equals_the_lanes_own(mesh, n_beams, n_rays):
         for name in ("x", "y", "z", "nx", "ny", "nz", "mat"):
             assert torch.equal(getattr(h, name).view(torch.int32), getattr(one, name).view(torch.int32)), name
     scene.close()
+
+
+@pytest.mark.parametrize("n_beams, n_rays", [(64, 64), (63, 65), (200, 3), (2, 500), (1, 130), (1100, 256)])
+def test_lines_and_patches_of_rays_agree(n_beams, n_rays):
+    """The reach of a cast decides, with the triangles' size, whether a wave
+    takes a line or a square patch of rays (and whether it shares a
+    traversal): hits within the shorter of two reaches are bit for bit the
+    same.  A floor of two triangles makes the longer reach count."""
+    import torch
+    import paper_2503_01074_amd as osm
+    v, t, m = _grid_plane(n=65, extent=32.0)
+    big = np.array([[-1e4, -1e4, -9], [1e4, -1e4, -9], [1e4, 1e4, -9], [-1e4, 1e4, -9]], np.float32)
+    scene = osm.Scene(np.concatenate([v, big]),
+                      np.concatenate([t, np.array([[0, 1, 2], [0, 2, 3]], np.int32) + len(v)]),
+                      np.concatenate([m, np.array([7, 8], np.int32)]))
+    pose = (np.zeros(3, np.float32), np.eye(3, dtype=np.float32))
+    fov = (float(np.float32(1.1)), float(np.float32(1.5)))
+    near, far = (osm.raycast(scene, [pose], n_beams, n_rays, *fov, tm)[0] for tm in (14.0, 1e4))
+    torch.cuda.synchronize()
+    hit = near.mat >= 0
+    assert bool(hit.any())
+    for name in ("x", "y", "z", "nx", "ny", "nz", "mat"):
+        assert torch.equal(getattr(near, name)[hit].view(torch.int32), getattr(far, name)[hit].view(torch.int32)), name
+    scene.close()
