@@ -523,8 +523,9 @@ enum {
  * thread, and keeps the fastest whose outputs agree with the default shape's
  * (1e-5 relative); results are cached per process and,
  * when the environment variable OCEANSIM_TUNE_CACHE names a file, in that
- * JSON file, keyed by GPU architecture, CU count and a size class of the
- * batch.  Tuning runs the launches, so it reads the inputs (which must hold
+ * JSON file, keyed by GPU architecture, CU count, a revision of the tuned
+ * kernels and a size class of the batch (its fans' density and operator
+ * layout and its camera frames among them).  Tuning runs the launches, so it reads the inputs (which must hold
  * representative returns) and writes the outputs and gradients.  When the
  * environment variable OCEANSIM_PLAN_SHAPE is set to "tile_bins,chunk"
  * (tile_bins 1..16384, chunk 512, 1024, 2048, 4096 or 8192 returns), plans

@@ -124,6 +124,19 @@ int pow2_at_least(long long v) {
     return p;
 }
 
+int fan_density(const oceansim_sonar_frame *frames, int n_frames, int &layout) {
+    double px = 0.0, nb = 0.0;
+    layout = 0;
+    for (int i = 0; i < n_frames; ++i) {
+        const int one = fan_operator_layout(frames[i]);
+        if (one != 0) px += (double)frames[i].fan_h * frames[i].fan_w;
+        nb += (double)frames[i].n_range * frames[i].n_azimuth;
+        layout = std::max(layout, one);
+    }
+    if (px > (layout == 2 ? 0.5 : 1.5) * nb) return 2;
+    return px > 0.2 * nb ? 1 : 0;
+}
+
 int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_rows, int n_mat, bool backward,
                SonarPlan &P, const Tuning *tune, bool force_table, bool pair_mode) {
     if (n_frames < 0) return fail(OCEANSIM_E_INVALID_ARG, "n_frames < 0");
@@ -221,18 +234,9 @@ int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_row
     // with 0.04 137, 92, 75.
     int fant_bpt = total_nb >= (16LL << 20) ? 4 : (total_nb >= (2LL << 20) ? 2 : 1);
     if (backward && fant_bpt > 1) {
-        double px = 0.0;
-        bool mirror = false;
-        for (int i = 0; i < n_frames; ++i) {
-            const int layout = fan_operator_layout(frames[i]);
-            if (layout != 0) px += (double)frames[i].fan_h * frames[i].fan_w;
-            mirror = mirror || layout == 2;
-        }
-        const double per_bin = px / (double)total_nb;
-        if (per_bin > (mirror ? 0.5 : 1.5))
-            fant_bpt = 1;
-        else if (per_bin > 0.2)
-            fant_bpt = 2;
+        int layout;
+        const int density = fan_density(frames, n_frames, layout);
+        if (density > 0) fant_bpt = density == 2 ? 1 : 2;
     }
     if (tune && (tune->fant_bpt == 1 || tune->fant_bpt == 2 || tune->fant_bpt == 4)) fant_bpt = tune->fant_bpt;
     for (int i = 0; i < n_frames; ++i) {

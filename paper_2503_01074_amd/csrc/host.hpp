@@ -55,6 +55,10 @@ inline int fan_operator_layout(const oceansim_sonar_frame &f) {
     return (f.fan_w % 2 == 0 && f.fan_w <= 65535 && f.fan_h <= 65535) ? 2 : 1;
 }
 
+// Class of a batch's fan pixels per polar bin, as operator rows per thread
+// depend on it (see plan_sonar): 0 few, 1, 2 many; layout: the largest of its frames'.
+int fan_density(const oceansim_sonar_frame *frames, int n_frames, int &layout);
+
 int fail(int code, const char *fmt, ...);
 int ok();
 int hip_fail(hipError_t e, const char *what);

@@ -217,6 +217,12 @@ int ilog2(long long v) {
     return e;
 }
 
+// Everything the choice depends on: the device, the sizes (powers of two), the
+// kernels' materials path, and since the camera's forward blocks ride in the
+// launches that are timed, and the operator rows per thread follow the fans'
+// density and layout, those too.  k: counted up when a change to these kernels
+// makes shapes timed before worth nothing (a file's older entries stay unread).
+constexpr int kTuneKernels = 2;
 std::string tune_key(const oceansim_plan *p) {
     int dev = 0, cus = 0;
     (void)hipGetDevice(&dev);
@@ -231,10 +237,13 @@ std::string tune_key(const oceansim_plan *p) {
         nb += (long long)f.n_range * f.n_azimuth;
         px += (long long)f.fan_h * f.fan_w;
     }
+    int layout = 0;
+    const int density = fan_density(p->sonar.data(), (int)p->sonar.size(), layout);
+    const int cam = p->fused && p->uf.blocks > 0 ? 1 + ilog2(p->uf.blocks) : 0;
     char buf[256];
-    snprintf(buf, sizeof buf, "%s/%dcu/s%d-r%d-b%d-f%d-m%d-bw%d", arch.c_str(), cus, ilog2(p->sonar.size()),
-             ilog2(n), ilog2(nb), ilog2(px), p->n_mat <= kLaneHistMats ? 0 : 1,
-             (p->flags & OCEANSIM_PLAN_BACKWARD) ? 1 : 0);
+    snprintf(buf, sizeof buf, "%s/%dcu/k%d-s%d-r%d-b%d-f%d-d%d-l%d-c%d-m%d-bw%d", arch.c_str(), cus, kTuneKernels,
+             ilog2(p->sonar.size()), ilog2(n), ilog2(nb), ilog2(px), density, layout, cam,
+             p->n_mat <= kLaneHistMats ? 0 : 1, (p->flags & OCEANSIM_PLAN_BACKWARD) ? 1 : 0);
     return buf;
 }
 

@@ -352,3 +352,39 @@ def test_plan_wide_shape_tiles_and_camera_in_one_launch(graph, monkeypatch):
     monkeypatch.setenv("OCEANSIM_PLAN_SHAPE", "100,3000")
     with pytest.raises(osm.OceansimError, match="OCEANSIM_PLAN_SHAPE"):
         osm.Plan(list(zip(geoms, hits)), sonar_params=params, refl=torch.as_tensor(refl).cuda())
+
+
+def test_autotune_keys_tell_plans_apart(tmp_path, monkeypatch):
+    """Plans of one size class that time different launches have entries of
+    their own: without and with camera frames, with fans of odd and even
+    width (plain and mirrored operators), and with fewer and more fan pixels per
+    bin on two sides of the heuristic's line."""
+    import json
+    import torch
+    import paper_2503_01074_amd as osm
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("OCEANSIM_TUNE_CACHE", str(cache))
+    _say("autotune keys")
+    st = W.Stream(913, 1)
+
+    def keys(fan_h, fan_w, cams):
+        spec = W.SonarSpec(r_min=0.5, r_max=30.0, n_range=130, n_azimuth=70, fan_h=fan_h, fan_w=fan_w,
+                           speckle_mode=W.SPECKLE_GAMMA, seed_lo=9, frame_id=1)
+        hits = W.make_hits(st, spec, 5003, n_materials=3)
+        image = torch.rand(3, 40, 60, device="cuda")
+        osm.Plan([(osm.SonarGeometry.from_spec(spec, param_row=0), osm.DeviceHits.from_host(hits))],
+                 [(image, image[0] + 1.0, 0)] * cams, sonar_params=osm.sonar_params([osm.sonar_params_from_spec(spec)]),
+                 refl=torch.as_tensor(hits.refl).cuda(),
+                 water=osm.water_params([([0.1] * 3, [0.1] * 3, [0.1] * 3)]) if cams else None, backward=True,
+                 autotune=True)
+        torch.cuda.synchronize()
+        return set(json.loads(cache.read_text()))
+
+    seen = set()
+    for case in ((60, 80, 0), (60, 80, 2), (60, 79, 0), (80, 59, 2)):   # 4800, 4740 and 4720 pixels on 9100 bins
+        now = keys(*case)
+        assert len(now - seen) >= 1, case
+        seen |= now
+    assert keys(60, 80, 0) == seen
+    # 4524 pixels: on the other side of the mirrored line at half a pixel a bin
+    assert len(keys(58, 78, 0) - seen) == 1
