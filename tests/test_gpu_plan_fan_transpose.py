@@ -312,3 +312,72 @@ def test_unused_fan_gradient_stays_in_its_cell():
             assert len(hit) <= 4 and (len(hit) == 0 or (hit % n_az).max() - (hit % n_az).min() <= 1)
             assert (np.unique(hit // n_az).size <= 2)
             np.testing.assert_array_equal(g[~bad], base[~bad])
+
+
+@pytest.mark.parametrize("n_range,n_az,Wd", [(6, 126, 140), (6, 127, 141), (5, 64, 90), (9, 31, 77), (40, 3, 30)])
+def test_fan_gradient_reaches_exactly_its_stencil(n_range, n_az, Wd):
+    """One return in the middle of every bin, each its own material: a NaN in
+    one fan pixel's gradient makes exactly the reflectivity gradients of the
+    bins of its stencil non-finite (those that the oracle's adjoint of that
+    pixel alone fills; bins of weight zero may join them) and changes no other.
+    Pixels of cells in all columns, at both ends of a wave's 63 operator rows,
+    at the mirrored half's last columns, and outside the sector."""
+    import torch
+    import paper_2503_01074_amd as osm
+    H = 100
+    spec = W.SonarSpec(r_min=1.0, r_max=9.0, n_range=n_range, n_azimuth=n_az, fan_h=H, fan_w=Wd,
+                       speckle_mode=W.SPECKLE_OFF)
+    cfg = SonarConfig.from_spec(spec)
+    b = np.arange(n_range * n_az)
+    r = spec.r_min + (b // n_az + 0.5) * (spec.r_max - spec.r_min) / n_range
+    phi = ((b % n_az + 0.5) / n_az - 0.5) * spec.fov_az
+    x, y, z = (r * np.cos(phi)).astype(np.float32), (r * np.sin(phi)).astype(np.float32), np.zeros(len(b), np.float32)
+    hits = W.SonarHits(x=x, y=y, z=z, nx=-x, ny=-y, nz=z.copy(), mat=b.astype(np.int32),
+                       refl=np.full(len(b), 0.5, np.float32))
+    plan = osm.Plan([(osm.SonarGeometry.from_spec(spec), osm.DeviceHits.from_host(hits))],
+                    sonar_params=osm.sonar_params([osm.sonar_params_from_spec(spec)]),
+                    refl=torch.as_tensor(hits.refl).cuda(), backward=True, bins=True)
+    plan.sonar_out[0]["grad_polar"].zero_()
+    g = torch.as_tensor(W.loss_weights((8911, n_az), (H, Wd))).cuda()
+    grad_fan = plan.sonar_out[0]["grad_fan"]
+
+    def gradient():
+        plan.backward()
+        torch.cuda.synchronize()
+        return plan.grad_refl.cpu().numpy()
+
+    grad_fan.copy_(g)
+    plan.forward()
+    base = gradient()
+    np.testing.assert_array_equal(plan.sonar_out[0]["bins"].cpu().numpy(), b)
+    assert np.isfinite(base).all()
+    # cells of the fan's pixels: first range row and column, from images of the row and column index
+    ones, _ = oracle.fan_forward(cfg, np.ones((n_range, n_az)))
+    inside = ones > 0.5
+    i0, j0 = (np.floor(oracle.fan_forward(cfg, im)[0] + 1e-9).astype(int) for im in
+              (np.repeat(np.arange(n_range), n_az).reshape(n_range, n_az), np.tile(np.arange(n_az), (n_range, 1))))
+    ncol = (n_az + 1) // 2 if Wd % 2 == 0 else n_az
+    row = np.where(inside & (j0 < ncol), i0 * ncol + j0, -1)
+    pixels = [np.argwhere(inside & (j0 == j)) for j in range(n_az)]                # every column
+    pixels += [np.argwhere((row >= 0) & (row % 63 == k)) for k in (0, 1, 61, 62)]   # around the ends of a wave
+    pixels += [np.argwhere(inside & (i0 == i) & (j0 >= ncol - 2) & (j0 <= ncol)) for i in range(n_range)]
+    pixels += [np.argwhere(~inside)]
+    assert len(pixels[0]) and len(pixels[max(n_az - 2, 0)]) and (n_range * ncol < 63 or all(map(len, pixels[n_az:n_az + 4])))
+    for v, u in np.unique(np.concatenate([q[[0, len(q) // 2, -1]] for q in pixels if len(q)]), axis=0):
+        delta = np.zeros((H, Wd), np.float32)
+        delta[v, u] = 1.0
+        want = np.flatnonzero(oracle.fan_adjoint(cfg, delta).reshape(-1))
+        grad_fan[v, u] = float("nan")
+        got = gradient()
+        grad_fan[v, u] = g[v, u]
+        bad = np.flatnonzero(~np.isfinite(got))
+        assert np.isin(want, bad).all(), (v, u)
+        if len(want) == 0:
+            assert len(bad) == 0, (v, u)
+            continue
+        assert len(bad) <= 4, (v, u)
+        for near, have in ((want // n_az, bad // n_az), (want % n_az, bad % n_az)):
+            assert have.min() >= near.max() - 1 and have.max() <= near.min() + 1, (v, u)
+        fine = np.setdiff1d(b, bad)
+        np.testing.assert_array_equal(got[fine], base[fine])
+    plan.close()
