@@ -2205,9 +2205,9 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
     // frames then run in a launch of their own
     const bool wide = g.chunk > 4096;
     const bool with_uw = uw && uw->blocks > 0;
-    int cam_fan = 0;
-    if constexpr (std::is_same_v<Src, Table<SonarDev>>)
-        if (with_uw && !wide) cam_fan = cam_in_fan(uw->blocks, g.fan_blocks);
+    constexpr bool kTable = std::is_same_v<Src, Table<SonarDev>>;
+    if (!kTable && with_uw) return hipErrorInvalidValue;   // camera frames come with plans, which launch from tables
+    const int cam_fan = with_uw && !wide ? cam_in_fan(uw->blocks, g.fan_blocks) : 0;
     const int cam_bin = with_uw ? uw->blocks - cam_fan : 0;
     if (g.bin_blocks > 0 || (with_uw && !wide)) {
         const size_t lds = (size_t)((g.max_tiles + 1 + 3) & ~3) * 4 + (size_t)g.chunk * 8;
@@ -2216,10 +2216,11 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
             OSIM_LAUNCH("k_bin", (k_bin<Src, kWideThreads, 16>), dim3(g.bin_blocks), dim3(kWideThreads), lds, st,
                         src, params, refl, n_mat);
         } else if (with_uw) {
-            OSIM_DISPATCH_R(g.chunk / kBlock,
-                            OSIM_LAUNCH("k_bin_uw", (k_bin_uw<Src, RR>), dim3(g.bin_blocks + cam_bin),
-                                        dim3(kBlock), lds, st, src, params, refl, n_mat, g.bin_blocks,
-                                        Table<UwDev>{uw->table, uw->n}, uw->params));
+            if constexpr (kTable)
+                OSIM_DISPATCH_R(g.chunk / kBlock,
+                                OSIM_LAUNCH("k_bin_uw", (k_bin_uw<Src, RR>), dim3(g.bin_blocks + cam_bin),
+                                            dim3(kBlock), lds, st, src, params, refl, n_mat, g.bin_blocks,
+                                            Table<UwDev>{uw->table, uw->n}, uw->params));
         } else {
             OSIM_DISPATCH_R(g.chunk / kBlock,
                             OSIM_LAUNCH("k_bin", (k_bin<Src, kBlock, RR>), dim3(g.bin_blocks), dim3(kBlock), lds,
@@ -2237,14 +2238,16 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
     if (with_uw && wide && wide_tiles) {
         // wide tiles and the camera forward side by side in one launch
         const int groups = (uw->blocks + 1) / 2;
-        if (col_regs)
-            OSIM_LAUNCH("k_tile_uw", (k_tile_uw<Src, true>), dim3(g.tile_blocks + groups), dim3(kWideThreads),
-                        tile_lds, st, src, params, refl, n_mat, g.tile_blocks, groups, Table<UwDev>{uw->table, uw->n},
-                        uw->params, uw->blocks);
-        else
-            OSIM_LAUNCH("k_tile_uw", (k_tile_uw<Src, false>), dim3(g.tile_blocks + groups), dim3(kWideThreads),
-                        tile_lds, st, src, params, refl, n_mat, g.tile_blocks, groups, Table<UwDev>{uw->table, uw->n},
-                        uw->params, uw->blocks);
+        if constexpr (kTable) {
+            if (col_regs)
+                OSIM_LAUNCH("k_tile_uw", (k_tile_uw<Src, true>), dim3(g.tile_blocks + groups), dim3(kWideThreads),
+                            tile_lds, st, src, params, refl, n_mat, g.tile_blocks, groups,
+                            Table<UwDev>{uw->table, uw->n}, uw->params, uw->blocks);
+            else
+                OSIM_LAUNCH("k_tile_uw", (k_tile_uw<Src, false>), dim3(g.tile_blocks + groups), dim3(kWideThreads),
+                            tile_lds, st, src, params, refl, n_mat, g.tile_blocks, groups,
+                            Table<UwDev>{uw->table, uw->n}, uw->params, uw->blocks);
+        }
     } else {
         if (with_uw && wide) {
             hipError_t e = uw_forward_table(uw->table, uw->n, uw->blocks, uw->params, st);
@@ -2263,7 +2266,7 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (cam_fan > 0) {
-        if constexpr (std::is_same_v<Src, Table<SonarDev>>)
+        if constexpr (kTable)
             OSIM_LAUNCH("k_fan_uw", k_fan_uw, dim3(g.fan_blocks + cam_fan), dim3(kBlock), 0, st, src,
                         fused_ratio(g.fan_blocks, cam_fan), Table<UwDev>{uw->table, uw->n}, uw->params, cam_bin);
         e = hipGetLastError();
@@ -2274,106 +2277,110 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
     return e;
 }
 
+// The polar gradient through the plans' fan operators.
+static hipError_t launch_fant(const Table<SonarDev> &src, const SonarGrid &g, const oceansim_sonar_params *params,
+                              double *part, int n_slots, float *grad_refl_zero, int n_mat, hipStream_t st) {
+#define OSIM_FANT(B, M)                                                                                         \
+    OSIM_LAUNCH("k_fant_bwd", (k_fant_bwd<Table<SonarDev>, B, M>), dim3(g.fant_blocks), dim3(kBlock), 0, st, src, \
+                params, part, n_slots, grad_refl_zero, n_mat)
+    switch (g.fant_bpt * 2 + (g.fant_mirror ? 1 : 0)) {
+        case 2: OSIM_FANT(1, false); break;
+        case 3: OSIM_FANT(1, true); break;
+        case 4: OSIM_FANT(2, false); break;
+        case 5: OSIM_FANT(2, true); break;
+        case 8: OSIM_FANT(4, false); break;
+        case 9: OSIM_FANT(4, true); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef OSIM_FANT
+    return hipGetLastError();
+}
+
+// The backward of a plan from its forward's material pairs.
+static hipError_t launch_pair_bwd(const Table<SonarDev> &src, const SonarGrid &g, const oceansim_sonar_params *params,
+                                  int n_rows, const float *refl, int n_mat, double *part, double *refl_part,
+                                  float *grad_params, float *grad_refl, hipStream_t st, SonarReduce *defer,
+                                  const UwBwdCompanion *uwb) {
+    // operator rows of the frames with a fan gradient, then one pair
+    // workgroup per forward tile; the camera backward in its own launch
+    const int n_slots = g.fant_blocks + g.tile_blocks;
+    hipError_t e = hipSuccess;
+    if (g.fant_blocks > 0) {
+        e = launch_fant(src, g, params, part, n_slots, nullptr, n_mat, st);
+        if (e != hipSuccess) return e;
+    }
+    const bool with_uw = uwb && uwb->blocks > 0;
+    const int groups = with_uw ? (uwb->blocks + 1) / 2 : 0;
+    if (g.tile_blocks > 0 && with_uw && g.tile_blocks >= groups) {
+        // the camera backward interleaved with the pair workgroups, where
+        // these are enough to hide it (the camera part keeps one
+        // channel's loads in flight, slower on its own)
+        if (g.wide_col_regs)
+            OSIM_LAUNCH("k_pair_uw_bwd", (k_pair_uw_bwd<Table<SonarDev>, true>), dim3(g.tile_blocks + groups),
+                        dim3(kWideThreads), (size_t)g.max_tile_bins * 4, st, src, params, refl, n_mat, part,
+                        g.fant_blocks, n_slots, refl_part, g.tile_blocks, groups, *uwb);
+        else
+            OSIM_LAUNCH("k_pair_uw_bwd", (k_pair_uw_bwd<Table<SonarDev>, false>), dim3(g.tile_blocks + groups),
+                        dim3(kWideThreads), (size_t)g.max_tile_bins * 4, st, src, params, refl, n_mat, part,
+                        g.fant_blocks, n_slots, refl_part, g.tile_blocks, groups, *uwb);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    } else {
+        if (g.tile_blocks > 0) {
+            if (g.wide_col_regs)
+                OSIM_LAUNCH("k_pair_bwd", (k_pair_bwd<Table<SonarDev>, true>), dim3(g.tile_blocks), dim3(kWideThreads),
+                            (size_t)g.max_tile_bins * 4, st, src, params, refl, n_mat, part, g.fant_blocks,
+                            n_slots, refl_part, g.tile_blocks);
+            else
+                OSIM_LAUNCH("k_pair_bwd", (k_pair_bwd<Table<SonarDev>, false>), dim3(g.tile_blocks), dim3(kWideThreads),
+                            (size_t)g.max_tile_bins * 4, st, src, params, refl, n_mat, part, g.fant_blocks,
+                            n_slots, refl_part, g.tile_blocks);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        if (with_uw) {
+            e = uw_backward_table(uwb->table, uwb->n, uwb->blocks, uwb->params, uwb->part, uwb->part_row, st);
+            if (e != hipSuccess) return e;
+        }
+    }
+    SonarReduce a;
+    a.part = part;
+    a.n_slots = n_slots;
+    a.n_rows = n_rows;
+    a.grad_params = grad_params;
+    a.refl_part = refl_part;
+    a.ret_slots = g.tile_blocks;
+    a.n_mat = n_mat;
+    a.grad_refl = grad_refl;
+    a.blocks = n_rows * OCEANSIM_SONAR_GRAD_WIDTH + n_mat;
+    if (defer) {
+        *defer = a;
+        return hipSuccess;
+    }
+    OSIM_LAUNCH("k_reduce_sonar", k_reduce_sonar, dim3(a.blocks), dim3(kBlock), 0, st, a);
+    return hipGetLastError();
+}
+
 template <class Src>
 static hipError_t launch_bwd(const Src &src, int n_frames, const SonarGrid &g,
                              const oceansim_sonar_params *params, int n_rows, const float *refl, int n_mat,
                              double *part, double *refl_part, float *grad_params, float *grad_refl,
                              hipStream_t st, SonarReduce *defer, const UwBwdCompanion *uwb) {
     const bool lane_hist = n_mat <= kLaneHistMats;
-    if (g.pair_bwd) {
-        // operator rows of the frames with a fan gradient, then one pair
-        // workgroup per forward tile; the camera backward in its own launch
-        const int n_slots = g.fant_blocks + g.tile_blocks;
-        hipError_t e = hipSuccess;
-        if (g.fant_blocks > 0) {
-#define OSIM_FANT(B, M)                                                                                     \
-    OSIM_LAUNCH("k_fant_bwd", (k_fant_bwd<Src, B, M>), dim3(g.fant_blocks), dim3(kBlock), 0, st, src, params, \
-                part, n_slots, (float *)nullptr, n_mat)
-            switch (g.fant_bpt * 2 + (g.fant_mirror ? 1 : 0)) {
-                case 2: OSIM_FANT(1, false); break;
-                case 3: OSIM_FANT(1, true); break;
-                case 4: OSIM_FANT(2, false); break;
-                case 5: OSIM_FANT(2, true); break;
-                case 8: OSIM_FANT(4, false); break;
-                case 9: OSIM_FANT(4, true); break;
-                default: return hipErrorInvalidValue;
-            }
-#undef OSIM_FANT
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        const bool with_uw = uwb && uwb->blocks > 0;
-        const int groups = with_uw ? (uwb->blocks + 1) / 2 : 0;
-        if (g.tile_blocks > 0 && with_uw && g.tile_blocks >= groups) {
-            // the camera backward interleaved with the pair workgroups, where
-            // these are enough to hide it (the camera part keeps one
-            // channel's loads in flight, slower on its own)
-            if (g.wide_col_regs)
-                OSIM_LAUNCH("k_pair_uw_bwd", (k_pair_uw_bwd<Src, true>), dim3(g.tile_blocks + groups),
-                            dim3(kWideThreads), (size_t)g.max_tile_bins * 4, st, src, params, refl, n_mat, part,
-                            g.fant_blocks, n_slots, refl_part, g.tile_blocks, groups, *uwb);
-            else
-                OSIM_LAUNCH("k_pair_uw_bwd", (k_pair_uw_bwd<Src, false>), dim3(g.tile_blocks + groups),
-                            dim3(kWideThreads), (size_t)g.max_tile_bins * 4, st, src, params, refl, n_mat, part,
-                            g.fant_blocks, n_slots, refl_part, g.tile_blocks, groups, *uwb);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        } else {
-            if (g.tile_blocks > 0) {
-                if (g.wide_col_regs)
-                    OSIM_LAUNCH("k_pair_bwd", (k_pair_bwd<Src, true>), dim3(g.tile_blocks), dim3(kWideThreads),
-                                (size_t)g.max_tile_bins * 4, st, src, params, refl, n_mat, part, g.fant_blocks,
-                                n_slots, refl_part, g.tile_blocks);
-                else
-                    OSIM_LAUNCH("k_pair_bwd", (k_pair_bwd<Src, false>), dim3(g.tile_blocks), dim3(kWideThreads),
-                                (size_t)g.max_tile_bins * 4, st, src, params, refl, n_mat, part, g.fant_blocks,
-                                n_slots, refl_part, g.tile_blocks);
-                e = hipGetLastError();
-                if (e != hipSuccess) return e;
-            }
-            if (with_uw) {
-                e = uw_backward_table(uwb->table, uwb->n, uwb->blocks, uwb->params, uwb->part, uwb->part_row, st);
-                if (e != hipSuccess) return e;
-            }
-        }
-        SonarReduce a;
-        a.part = part;
-        a.n_slots = n_slots;
-        a.n_rows = n_rows;
-        a.grad_params = grad_params;
-        a.refl_part = refl_part;
-        a.ret_slots = g.tile_blocks;
-        a.n_mat = n_mat;
-        a.grad_refl = grad_refl;
-        a.blocks = n_rows * OCEANSIM_SONAR_GRAD_WIDTH + n_mat;
-        if (defer) {
-            *defer = a;
-            return hipSuccess;
-        }
-        OSIM_LAUNCH("k_reduce_sonar", k_reduce_sonar, dim3(a.blocks), dim3(kBlock), 0, st, a);
-        return hipGetLastError();
-    }
+    constexpr bool kTable = std::is_same_v<Src, Table<SonarDev>>;   // operators, pairs and camera frames come with plans
+    if (!kTable && (g.pair_bwd || g.use_fant || (uwb && uwb->blocks > 0))) return hipErrorInvalidValue;
+    if constexpr (kTable)
+        if (g.pair_bwd)
+            return launch_pair_bwd(src, g, params, n_rows, refl, n_mat, part, refl_part, grad_params, grad_refl, st,
+                                   defer, uwb);
     // partial-sum slots: polar workgroups (tiles, or bin blocks through the
     // transposed fan operators), then return chunks
     const int polar_blocks = g.use_fant ? g.fant_blocks : g.tile_b_blocks;
     const int n_slots = polar_blocks + g.ret_blocks + g.row_blocks;
     hipError_t e = hipSuccess;
     if (g.use_fant && g.fant_blocks > 0) {
-        float *gz = lane_hist ? (float *)nullptr : grad_refl;
-#define OSIM_FANT(B, M)                                                                                     \
-    OSIM_LAUNCH("k_fant_bwd", (k_fant_bwd<Src, B, M>), dim3(g.fant_blocks), dim3(kBlock), 0, st, src, params, \
-                part, n_slots, gz, n_mat)
-        switch (g.fant_bpt * 2 + (g.fant_mirror ? 1 : 0)) {
-            case 2: OSIM_FANT(1, false); break;
-            case 3: OSIM_FANT(1, true); break;
-            case 4: OSIM_FANT(2, false); break;
-            case 5: OSIM_FANT(2, true); break;
-            case 8: OSIM_FANT(4, false); break;
-            case 9: OSIM_FANT(4, true); break;
-            default: return hipErrorInvalidValue;
-        }
-#undef OSIM_FANT
-        e = hipGetLastError();
+        if constexpr (kTable)
+            e = launch_fant(src, g, params, part, n_slots, lane_hist ? (float *)nullptr : grad_refl, n_mat, st);
         if (e != hipSuccess) return e;
     } else if (!g.use_fant && g.tile_b_blocks > 0) {
         if (g.all_saved)
@@ -2402,14 +2409,11 @@ static hipError_t launch_bwd(const Src &src, int n_frames, const SonarGrid &g,
     double *rp = lane_hist ? refl_part : nullptr;
     float *ga = lane_hist ? nullptr : grad_refl;
     if (fuse) {
-        if constexpr (!std::is_same_v<Src, Table<SonarDev>>) {
-            return hipErrorInvalidValue;   // camera frames come with plans, which launch from tables
-        } else {
+        if constexpr (kTable)
             OSIM_DISPATCH_R(g.ret_chunk / kBlock,
                             OSIM_LAUNCH("k_ret_uw_bwd", (k_ret_uw_bwd<Src, RR>), dim3(g.ret_blocks + uw_blocks),
                                         dim3(kBlock), lds, st, src, params, refl, n_mat, part, polar_blocks, n_slots,
                                         rp, ga, g.ret_blocks, *uwb));
-        }
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     } else {

@@ -44,3 +44,14 @@ def test_plan_hot_kernels_have_no_spills():
         assert ks[k].get("scratch_bytes_per_lane", 0) == 0, k
         assert ks[k].get("vgpr_spills", 0) == 0, k
         assert ks[k].get("waves_per_simd", 0) >= 2, k
+
+
+@pytest.mark.skipif(not REPORTS, reason="library not built in this tree")
+def test_kernels_of_plans_are_built_for_tables_alone():
+    """Plans launch from frame tables only: the kernels that only they launch
+    have no variant for a frame passed by value."""
+    ks = _kernels()
+    plans = [k for k in ks if any(n in k for n in ("k_fant_bwd", "k_pair_bwd", "k_pair_uw_bwd", "k_ret_uw_bwd", "k_bin_uw",
+                                                  "k_tile_uw", "k_fan_uw"))]
+    assert len(plans) >= 20
+    assert not [k for k in plans if "3OneINS" in k]
