@@ -525,8 +525,9 @@ enum {
  * when the environment variable OCEANSIM_TUNE_CACHE names a file, in that
  * JSON file, keyed by GPU architecture, CU count, a revision of the tuned
  * kernels and a size class of the batch (its fans' density and operator
- * layout and its camera frames among them).  Tuning runs the launches, so it reads the inputs (which must hold
- * representative returns) and writes the outputs and gradients.  When the
+ * layout and its camera frames among them).  Tuning runs the launches, so it
+ * reads the inputs (which must hold representative returns) and writes the
+ * outputs and gradients.  When the
  * environment variable OCEANSIM_PLAN_SHAPE is set to "tile_bins,chunk"
  * (tile_bins 1..16384, chunk 512, 1024, 2048, 4096 or 8192 returns), plans
  * take that forward tile target and binning chunk instead of the heuristic or
@@ -548,9 +549,9 @@ int oceansim_plan_forward(oceansim_plan *plan, void *stream);
 int oceansim_plan_backward(oceansim_plan *plan, void *stream);
 
 /* Launch shapes in use: {forward tile bins, returns per chunk, operator rows
- * per thread of a backward workgroup times its 256 threads (a row is a polar
- * bin, or a bin and its mirror bin; 0 without a sonar backward), graphs in
- * use (0/1)}. */
+ * per thread of the backward through the fan operators, times the 256 threads
+ * of a workgroup (a row is a polar bin, or a bin and its mirror bin; 252 of the
+ * 256 threads have rows; 0 without a sonar backward), graphs in use (0/1)}. */
 int oceansim_plan_shape(const oceansim_plan *plan, int32_t shape[4]);
 
 /* Frees the plan's device memory and graphs (after synchronising the

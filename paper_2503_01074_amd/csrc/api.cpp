@@ -231,7 +231,8 @@ int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_row
     // 0.69 30, 31, 45, with 3.7 53, 119, 475; 2048^2 with 0.04 90, 74, 81, with
     // 0.39 97, 86, 101, with 0.93 120, 116, 169.  Plain operators (half the
     // gathers a row): 1024^2 with 1.5 50, 50, 101, with 3.7 77, 121, 429; 2048^2
-    // with 0.04 137, 92, 75.
+    // with 0.04 137, 92, 75.  (Four rows of a mirrored operator are nowhere the
+    // fastest, by up to a tenth at 0.04; plans that are tuned time all three.)
     int fant_bpt = total_nb >= (16LL << 20) ? 4 : (total_nb >= (2LL << 20) ? 2 : 1);
     if (backward && fant_bpt > 1) {
         int layout;

@@ -125,7 +125,7 @@ struct SonarDev {
     double tan_half_az;         // tan(fov_az / 2) (fans need fov_az <= pi)
     double inv_r_max;           // 1 / r_max
     float scale_phi_f, half_az_f;
-    float az_edge;              // twice the bound of the FP32 azimuth's error, in cells (see return_bin)
+    float az_edge;              // azimuths this close to a cell edge, in cells, are redone in FP64 (see return_bin)
     int half_w;                 // fan pixel pairs per row: ceil(fan_w / 2)
     gptr<int4> stencil;         // saved fan stencils [fan_h][half_w] or nullptr
     gptr<double2> cols;         // forward fan: {sin, cos} of each column-centre azimuth [n_az]
@@ -399,12 +399,14 @@ __device__ __forceinline__ float speckle_factor(const SonarDev &f, uint32_t b, f
 // bin from an FP32 atan2 that is redone in FP64 when it lands near a cell
 // edge, elevation cone test in FP64.  Returns the frame-linear bin or -1, and
 // the FP64 range.
-// The FP32 azimuth in cells is off by less than 3.5e-7 N_phi (three ulps of
-// the angle and half an ulp each of the half sector, the sum, the scale and
-// the product; 2.0e-7 N_phi at most over 3e9 directions and fields of view from 0.01 to
-// 2 pi), so "near" is 7e-7 N_phi: with a fixed 2e-3 every fourth wave of 64
-// returns redid its azimuths, at 2048 columns one in eleven does now (with
-// return_intensity's cosine: k_bin over 33.5 M returns 260 -> 253 us).
+// The FP32 azimuth in cells is off by less than 3.9e-7 N_phi: 3 x 2^-24 N_phi
+// for three ulps of the angle, 2^-25 for the half sector's rounding, 2^-24 each
+// for those of the sum, the scale and the product (2.0e-7 N_phi at most over
+// 3e9 directions and fields of view from 0.01 to 2 pi).  "Near" is 7e-7 N_phi,
+// 1.8 times that, and enough for an arctangent off by six ulps (5.7e-7).  With a
+// fixed 2e-3 every fourth wave of 64 returns redid its azimuths, at 2048 columns
+// one in six does now (with return_intensity's cosine: k_bin over 33.5 M returns
+// 260 -> 253 us).
 // --------------------------------------------------------------------------
 __device__ __forceinline__ int return_bin(const SonarDev &f, float xf, float yf, float zf, int m,
                                           int n_mat, double &r) {
@@ -462,8 +464,6 @@ __device__ __forceinline__ float return_intensity(const SonarDev &f, float xf, f
     return refl * c * e;
 }
 
-// Additive speckle geometry of bin (i, j): R_i = r_i^2 / r_max^2 and the
-// bin-centre azimuth phi_j (Eq. 3).
 // b / n and the remainder for 0 <= b < 2^24 (a polar bin) by inv = 1.0f / n, a
 // third of an integer division's instructions: b is exact in float, and the
 // product, two roundings of 2^-24 away from the quotient, within 2/3 of it for
@@ -482,6 +482,9 @@ __host__ __device__ __forceinline__ int bin_row(int b, int n, float inv, int &co
     column = j;
     return i;
 }
+
+// Additive speckle geometry of bin (i, j): R_i = r_i^2 / r_max^2 and the
+// bin-centre azimuth phi_j (Eq. 3).
 __device__ __forceinline__ float range_ramp(const SonarDev &f, int i) {
     double ri = f.r_min + ((double)i + 0.5) * f.dr;
     double q = ri * f.inv_r_max;

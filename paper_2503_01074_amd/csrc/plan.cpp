@@ -993,7 +993,8 @@ int oceansim_plan_shape(const oceansim_plan *p, int32_t shape[4]) {
     if (!p || !shape) return fail(OCEANSIM_E_INVALID_ARG, "NULL argument");
     shape[0] = p->sf.grid.max_tile_bins;
     shape[1] = p->sf.grid.chunk;
-    // bins per backward workgroup
+    // operator rows per thread times the workgroup's threads (a workgroup takes
+    // kFantRows times them: each wave's first lane has no rows of its own)
     shape[2] = (p->flags & OCEANSIM_PLAN_BACKWARD) && !p->sonar.empty() ? kBlock * p->sb.grid.fant_bpt : 0;
     shape[3] = p->g_fwd ? 1 : 0;
     return ok();

@@ -421,7 +421,8 @@ __device__ __forceinline__ void packet_traverse(const Ray &q, float o0, float o1
 // stack's entries live in the lanes of three registers.  8 x (2048 x 1024)
 // rays on a seabed of 130,242 triangles: 985 us with a traversal per lane over
 // 64 rays of one beam, 640 us with one per wave over 8 x 8 patches and planes
-// picked by scalar selects, 476 us with the octants (35 G rays/s).
+// picked by scalar selects, 476 us with the octants, 411 us with runs of tiles per
+// XCD (41 G rays/s).
 __global__ __launch_bounds__(kRayThreads) void k_raycast_packet(RayGroup g, gptr<const float4> nodes,
                                                                 gptr<const float4> tris, int root, int empty) {
     static_assert(kBvhMaxDepth <= kWave, "a stack entry per lane");

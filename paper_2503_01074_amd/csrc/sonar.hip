@@ -1781,8 +1781,10 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
 // itself.  The entries of a wave's cells are contiguous: the wave reads them
 // in coalesced 64-entry chunks (lane k takes entry k of a chunk), so its fan
 // gathers are the neighbouring pixels of neighbouring bins; weights and pixels go
-// to the wave's slice of LDS, and each lane then sums its own cells' runs while the
-// next round's entries are on their way.
+// to the wave's slice of LDS, and each lane then sums its own cells' runs.  The
+// first round's entries are on their way under the speckle draws; those of
+// later rounds are hidden by the SIMD's other waves alone (a round ahead they
+// cost registers and gained nothing).
 // With a mirrored operator (even fan width) a thread's rows are bins of the
 // left half of the azimuth columns: each entry is gathered at its pixel and
 // at the mirrored pixel, giving the row's bin and its mirror bin at once from
