@@ -133,6 +133,7 @@ int fan_density(const oceansim_sonar_frame *frames, int n_frames, int &layout) {
         nb += (double)frames[i].n_range * frames[i].n_azimuth;
         layout = std::max(layout, one);
     }
+    if (px > 8.0 * nb) return 3;
     if (px > (layout == 2 ? 0.5 : 1.5) * nb) return 2;
     return px > 0.2 * nb ? 1 : 0;
 }
@@ -234,11 +235,9 @@ int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_row
     // with 0.04 137, 92, 75.  (Four rows of a mirrored operator are nowhere the
     // fastest, by up to a tenth at 0.04; plans that are tuned time all three.)
     int fant_bpt = total_nb >= (16LL << 20) ? 4 : (total_nb >= (2LL << 20) ? 2 : 1);
-    if (backward && fant_bpt > 1) {
-        int layout;
-        const int density = fan_density(frames, n_frames, layout);
-        if (density > 0) fant_bpt = density == 2 ? 1 : 2;
-    }
+    int layout = 0;
+    const int density = backward ? fan_density(frames, n_frames, layout) : 0;
+    if (fant_bpt > 1 && density > 0) fant_bpt = density >= 2 ? 1 : 2;
     if (tune && (tune->fant_bpt == 1 || tune->fant_bpt == 2 || tune->fant_bpt == 4)) fant_bpt = tune->fant_bpt;
     for (int i = 0; i < n_frames; ++i) {
         const oceansim_sonar_frame &fr = frames[i];
@@ -352,6 +351,7 @@ int plan_sonar(const oceansim_sonar_frame *frames, int n_frames, int n_param_row
     P.grid.fant_bpt = fant_bpt;
     P.grid.use_fant = 0;
     P.grid.pair_bwd = backward && pair_mode ? 1 : 0;
+    P.grid.fant_dense = fant_bpt == 1 && density == 3 ? 1 : 0;
     P.grid.fant_mirror = 0;
     for (const SonarDev &d : P.dev) P.grid.fant_mirror |= d.ft_mirror;
     P.grid.all_saved = 1;

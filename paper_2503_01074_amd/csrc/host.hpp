@@ -56,7 +56,8 @@ inline int fan_operator_layout(const oceansim_sonar_frame &f) {
 }
 
 // Class of a batch's fan pixels per polar bin, as operator rows per thread
-// depend on it (see plan_sonar): 0 few, 1, 2 many; layout: the largest of its frames'.
+// and its rounds depend on it (see plan_sonar, k_fant_bwd): 0 few to 3 many; layout: the
+// largest of its frames'.
 int fan_density(const oceansim_sonar_frame *frames, int n_frames, int &layout);
 
 int fail(int code, const char *fmt, ...);

@@ -53,6 +53,7 @@ struct SonarGrid {
     int fant_bpt;        // operator rows per thread of those workgroups: 1, 2 or 4
     int use_fant;        // backward through the frames' transposed fan operators instead of polar tiles
     int fant_mirror;     // some frame's operator has the mirrored layout
+    int fant_dense;      // one row per thread, and many entries in a row
     int row_blocks;      // backward: one workgroup per range row of the range-normalised frames
     int max_rows_per_tile;   // forward: widest tile (rows) of a range-normalised frame; 0: none
     int pair_bwd;        // backward from the forward's material pairs (k_pair_bwd, one workgroup per forward tile)

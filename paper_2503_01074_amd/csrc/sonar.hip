@@ -1793,12 +1793,17 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
 // Against entries by bins, multiplied before LDS (a frame of 1024 x 1024 bins
 // and as dense a fan; 12 of them; 20 of 512 x 512): 17.8, 130, 52 us -> 16.7,
 // 111, 52 with 0.6 of the cache accesses.  Two chunks a round keep eight waves
-// on a SIMD (56 registers); four 16.6, 120, 53.  Neighbouring range rows read
+// on a SIMD (56 registers); four 16.6, 120, 53 (see kFantChunks).  Neighbouring range rows read
 // the same fan lines, so runs of 16 workgroups go to one XCD: 15.8, 107, 43.5
 // (8: 16.6, 108, 44.8; 64: 15.7, 108, 47.4).  What bounds it now is the VALU,
 // mostly the speckle of every bin and the lanes' unequal runs.
 // ---------------------------------------------------------------------------
-constexpr int kFantChunks = 2;    // 64-entry chunks staged per round
+// 64-entry chunks staged per round: two while the rows are short; where a cell
+// has eight fan pixels and more a round of two holds the entries of few lanes,
+// which sum them while the others wait, so eight (four waves on a SIMD, but
+// 12 frames of 256 x 256 bins with 8 pixels a bin 52 -> 45 us, 20 159 -> 96, 122 2374 ->
+// 1231; with 5.7 on 8 frames of 1024 x 1024 222 -> 243).
+constexpr int kFantChunks = 2, kFantChunksDense = 8;
 constexpr int kFantXcdRun = 16;   // consecutive workgroups one XCD takes
 constexpr size_t kFuseLdsBytes = 16384;   // LDS of a return-gather workgroup that camera workgroups may share
 
@@ -1813,10 +1818,10 @@ __device__ __forceinline__ double wave_shift_up(double v) {
 
 // MIRROR: the batch has mirrored operators (their rows produce two bins;
 // without any, the kernel keeps one output per row and fewer registers).
-template <class Src, int BPT, bool MIRROR>
+template <class Src, int BPT, bool MIRROR, int CHUNKS>
 __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_sonar_params *params, double *part,
                                                      int n_slots, float *grad_refl_zero, int n_mat_zero) {
-    __shared__ float4 staged[kBlock / kWave][kFantChunks * kWave];   // {w0, w1, dL/dF, dL/dF mirrored}
+    __shared__ float4 staged[kBlock / kWave][CHUNKS * kWave];   // {w0, w1, dL/dF, dL/dF mirrored}
     int local;
     const int bid = xcd_grouped_id<kFantXcdRun>(blockIdx.x, gridDim.x);
     const int fi = src.locate(bid, KFANT, local);
@@ -1913,11 +1918,11 @@ __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_son
     // The entries of the round that starts at r0.  Every lane loads (past the
     // end it re-reads the wave's last entry, which no cell sums); a chunk pair
     // that is wholly past the end is not read.
-    unsigned px[kFantChunks];
-    float2 w[kFantChunks];
+    unsigned px[CHUNKS];
+    float2 w[CHUNKS];
     auto load_entries = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = 0; c < kFantChunks; ++c)
+        for (int c = 0; c < CHUNKS; ++c)
             if (c % 2 == 0 ? r0 + c * kWave < w_hi : r0 + (c - 1) * kWave < w_hi) {
                 const int e = r0 + c * kWave + lane;
                 const gptr<const FanEntry> q = f.ft_ent + (e < w_hi ? e : w_hi - 1);
@@ -1960,11 +1965,11 @@ __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_son
     auto rounds = [&](auto mirror) __attribute__((always_inline)) {
         constexpr bool MIR = decltype(mirror)::value;
         float4 *slice = staged[wave];
-        for (int r0 = w_lo; r0 < w_hi; r0 += kFantChunks * kWave) {
-            float gv[kFantChunks], gm[kFantChunks];
+        for (int r0 = w_lo; r0 < w_hi; r0 += CHUNKS * kWave) {
+            float gv[CHUNKS], gm[CHUNKS];
             if (r0 != w_lo) load_entries(r0);
 #pragma unroll
-            for (int c = 0; c < kFantChunks; ++c)
+            for (int c = 0; c < CHUNKS; ++c)
                 if (r0 + (c & ~1) * kWave < w_hi) {
                     if constexpr (MIR) {
                         const unsigned u = px[c] & 0xffffu;
@@ -1977,7 +1982,7 @@ __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_son
                     }
                 }
 #pragma unroll
-            for (int c = 0; c < kFantChunks; ++c)
+            for (int c = 0; c < CHUNKS; ++c)
                 if (r0 + (c & ~1) * kWave < w_hi)
                     slice[c * kWave + lane] = make_float4(w[c].x, w[c].y, gv[c], gm[c]);
             // the wave's own LDS writes, then its reads (no other wave touches the slice)
@@ -1985,7 +1990,7 @@ __global__ __launch_bounds__(kBlock) void k_fant_bwd(Src src, const oceansim_son
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             const int a = p[0] > r0 ? p[0] : r0;
-            const int z = p[BPT] < r0 + kFantChunks * kWave ? p[BPT] : r0 + kFantChunks * kWave;
+            const int z = p[BPT] < r0 + CHUNKS * kWave ? p[BPT] : r0 + CHUNKS * kWave;
             for (int e = a; e < z; ++e) {
                 const float4 q = slice[e - r0];
                 if constexpr (BPT == 1) {
@@ -2282,9 +2287,17 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
 // The polar gradient through the plans' fan operators.
 static hipError_t launch_fant(const Table<SonarDev> &src, const SonarGrid &g, const oceansim_sonar_params *params,
                               double *part, int n_slots, float *grad_refl_zero, int n_mat, hipStream_t st) {
-#define OSIM_FANT(B, M)                                                                                         \
-    OSIM_LAUNCH("k_fant_bwd", (k_fant_bwd<Table<SonarDev>, B, M>), dim3(g.fant_blocks), dim3(kBlock), 0, st, src, \
+#define OSIM_FANT_CHUNKS(B, M, C)                                                                                  \
+    OSIM_LAUNCH("k_fant_bwd", (k_fant_bwd<Table<SonarDev>, B, M, C>), dim3(g.fant_blocks), dim3(kBlock), 0, st, src, \
                 params, part, n_slots, grad_refl_zero, n_mat)
+#define OSIM_FANT(B, M) OSIM_FANT_CHUNKS(B, M, kFantChunks)
+    if (g.fant_dense) {
+        if (g.fant_mirror)
+            OSIM_FANT_CHUNKS(1, true, kFantChunksDense);
+        else
+            OSIM_FANT_CHUNKS(1, false, kFantChunksDense);
+        return hipGetLastError();
+    }
     switch (g.fant_bpt * 2 + (g.fant_mirror ? 1 : 0)) {
         case 2: OSIM_FANT(1, false); break;
         case 3: OSIM_FANT(1, true); break;
@@ -2295,6 +2308,7 @@ static hipError_t launch_fant(const Table<SonarDev> &src, const SonarGrid &g, co
         default: return hipErrorInvalidValue;
     }
 #undef OSIM_FANT
+#undef OSIM_FANT_CHUNKS
     return hipGetLastError();
 }
 

@@ -314,7 +314,8 @@ def test_unused_fan_gradient_stays_in_its_cell():
             np.testing.assert_array_equal(g[~bad], base[~bad])
 
 
-@pytest.mark.parametrize("n_range,n_az,Wd", [(6, 126, 140), (6, 127, 141), (5, 64, 90), (9, 31, 77), (40, 3, 30)])
+@pytest.mark.parametrize("n_range,n_az,Wd", [(6, 126, 140), (6, 127, 141), (5, 64, 90), (9, 31, 77), (40, 3, 30),
+                                             (40, 126, 140), (30, 127, 141)])
 def test_fan_gradient_reaches_exactly_its_stencil(n_range, n_az, Wd):
     """One return in the middle of every bin, each its own material: a NaN in
     one fan pixel's gradient makes exactly the reflectivity gradients of the
