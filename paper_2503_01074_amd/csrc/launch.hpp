@@ -68,11 +68,12 @@ constexpr int kFantRows = kBlock / kWave * (kWave - 1);
 
 // Camera frames carried along in the forward sonar launches of a plan
 // with both kinds of frames: device frame table, workgroups (kBlock threads
-// each) and the water parameters.
+// each), their pixels in all and the water parameters.
 struct UwCompanion {
     const UwDev *table = nullptr;
     int n = 0;
     int blocks = 0;
+    long long pixels = 0;
     const oceansim_water_params *params = nullptr;
 };
 

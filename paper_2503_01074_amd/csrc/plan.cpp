@@ -71,11 +71,12 @@ __global__ void k_count_disagree(const float *a, const float *b, long long n, fl
     if (local) atomicAdd(bad, local);
 }
 
-UwCompanion companion(oceansim_plan *p) {
+UwCompanion companion(const oceansim_plan *p, const UwDev *table) {
     UwCompanion c;
-    c.table = reinterpret_cast<const UwDev *>(p->ws_uf + p->uf.off_table);
+    c.table = table;
     c.n = (int)p->camera.size();
     c.blocks = p->uf.blocks;
+    for (const UwDev &d : p->uf.dev) c.pixels += d.npix;
     c.params = p->wp;
     return c;
 }
@@ -106,7 +107,7 @@ hipError_t camera_backward(oceansim_plan *p, hipStream_t st) {
 
 hipError_t launch_forward(oceansim_plan *p, hipStream_t st) {
     if (p->sonar.empty()) return camera_forward(p, st);
-    const UwCompanion c = p->fused ? companion(p) : UwCompanion{};
+    const UwCompanion c = p->fused ? companion(p, reinterpret_cast<const UwDev *>(p->ws_uf + p->uf.off_table)) : UwCompanion{};
     hipError_t e = sonar_forward_table(reinterpret_cast<const SonarDev *>(p->ws_sf + p->sf.off_table),
                                        (int)p->sonar.size(), p->sf.grid, p->sp, p->refl, p->n_mat, st,
                                        p->fused ? &c : nullptr);
@@ -338,10 +339,7 @@ int autotune(oceansim_plan *p, hipStream_t st) {
             if (uw_table) (void)hipFree(uw_table);
             return hip_fail(ue, "autotune camera table");
         }
-        uwc.table = uw_table;
-        uwc.n = (int)p->camera.size();
-        uwc.blocks = p->uf.blocks;
-        uwc.params = p->wp;
+        uwc = companion(p, uw_table);
     }
     hipError_t e = hipMalloc(&tmp, ws + 256);
     if (e != hipSuccess) {

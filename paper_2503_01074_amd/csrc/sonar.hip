@@ -2195,10 +2195,17 @@ __global__ __launch_bounds__(kBlock) void k_reduce_sonar(SonarReduce a) {
 // are still binned, and in the fan's launch would only lengthen it:
 //   1 x 512 x 256 + 540p (507 blocks) 17.7 -> 18.1
 //   1 x 512 x 512 + 720p (900 blocks) 18.9 -> 19.1
+// Nor does a camera of more than four times the fans' pixels split well: its
+// stream bounds either launch, and the tiles between them run alone (images that
+// change with each launch; the same eight 1080p images every time 93 -> 104):
+//   4 x 512 x 512 + 4 x 1080p, 4.0 times 64.1 -> 63.4   16 images of 720p, 1.8: 121 -> 114
+//   16 x 300 x 200 + 8 x 1080p, 5.8      107.4 -> 109.1   9 images, 6.5: 122 -> 126
+//   4 x 512 x 512, fans 333 x 777, + 16 x 1080p, 32      193.7 -> 197.7
 // No more blocks than there are fan workgroups to ride with, and the sum within
 // a launch's 2^32 threads.
-static int cam_in_fan(int cam_blocks, int fan_blocks) {
+static int cam_in_fan(int cam_blocks, long long cam_pixels, int fan_blocks) {
     if (cam_blocks < 1024 || fan_blocks >= (1 << 23)) return 0;
+    if (cam_pixels > 4LL * fan_blocks * (2 * kFanTileU * kFanTileV)) return 0;
     const long long share = (long long)cam_blocks * 5 / 8;
     return (int)(share < fan_blocks ? share : fan_blocks);
 }
@@ -2214,7 +2221,7 @@ static hipError_t launch_fwd(const Src &src, const SonarGrid &g, const oceansim_
     const bool with_uw = uw && uw->blocks > 0;
     constexpr bool kTable = std::is_same_v<Src, Table<SonarDev>>;
     if (!kTable && with_uw) return hipErrorInvalidValue;   // camera frames come with plans, which launch from tables
-    const int cam_fan = with_uw && !wide ? cam_in_fan(uw->blocks, g.fan_blocks) : 0;
+    const int cam_fan = with_uw && !wide ? cam_in_fan(uw->blocks, uw->pixels, g.fan_blocks) : 0;
     const int cam_bin = with_uw ? uw->blocks - cam_fan : 0;
     if (g.bin_blocks > 0 || (with_uw && !wide)) {
         const size_t lds = (size_t)((g.max_tiles + 1 + 3) & ~3) * 4 + (size_t)g.chunk * 8;

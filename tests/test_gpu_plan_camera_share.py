@@ -67,3 +67,41 @@ def test_camera_split_over_binning_and_fan(name, fans, images, graph):
             got = o["out"].cpu().numpy()
             assert_image_close(got, want, "%s camera %d rep %d" % (name, k, rep))
     plan.close()
+
+
+@pytest.mark.parametrize("side,split", [(600, True), (480, False)])
+def test_large_cameras_ride_in_the_binning_alone(side, split):
+    """A camera frame of 1200 x 1200 pixels (1407 workgroups) is split over
+    the binning and the fan launch only if the fan has a quarter of its
+    pixels: 600 x 610, but not 480 x 610."""
+    import torch
+    import paper_2503_01074_amd as osm
+    from paper_2503_01074_amd import _lib
+    print("[case] camera split, fan side %d" % side, flush=True)
+    st = W.Stream(962, side)
+    spec = W.SonarSpec(r_min=0.5, r_max=11.0, n_range=64, n_azimuth=48, fan_h=side, fan_w=610,
+                       speckle_mode=W.SPECKLE_OFF)
+    hits = W.make_hits(st, spec, 3000, n_materials=5)
+    cam = W.make_camera(st, 1200, 1200)
+    water = W.make_water(st)
+    plan = osm.Plan([(osm.SonarGeometry.from_spec(spec), osm.DeviceHits.from_host(hits))],
+                    [(torch.as_tensor(cam.J).cuda(), torch.as_tensor(cam.depth).cuda(), 0)],
+                    sonar_params=osm.sonar_params([osm.sonar_params_from_spec(spec)]),
+                    refl=torch.as_tensor(hits.refl).cuda(),
+                    water=osm.water_params([(water.beta_d, water.beta_b, water.b_inf)]))
+    _lib.oceansim_trace_enable(True)
+    try:
+        plan.forward()
+        torch.cuda.synchronize()
+        names = set(_lib.oceansim_trace_summary())
+    finally:
+        _lib.oceansim_trace_enable(False)
+    assert "k_bin_uw" in names and ("k_fan_uw" if split else "k_fan") in names
+    assert ("k_fan" if split else "k_fan_uw") not in names
+    want = oracle.sonar_forward(SonarConfig.from_spec(spec), hits, hits.refl)
+    o = plan.sonar_out[0]
+    assert_image_close(o["polar"].cpu().numpy(), want["out"], "polar")
+    assert_image_close(o["fan"].cpu().numpy(), want["fan"], "fan", mask=~want["ambiguous"])
+    image = oracle.uw_forward(cam.J, cam.depth, water.beta_d, water.beta_b, water.b_inf)
+    assert_image_close(plan.camera_out[0]["out"].cpu().numpy(), image, "camera")
+    plan.close()
