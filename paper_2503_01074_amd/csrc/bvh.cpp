@@ -216,8 +216,8 @@ int build_bvh(const float *vertices, long long n_vertices, const int32_t *triang
     B.prims.reserve((size_t)n_triangles);
     std::vector<long long> kept;
     kept.reserve((size_t)n_triangles);
-    std::vector<double> area;
-    area.reserve((size_t)n_triangles);
+    std::vector<double> area;   // of a few thousand triangles, evenly taken
+    const long long every = 1 + n_triangles / 4096;
     for (long long f = 0; f < n_triangles; ++f) {
         double v[3][3];
         for (int j = 0; j < 3; ++j) {
@@ -245,8 +245,8 @@ int build_bvh(const float *vertices, long long n_vertices, const int32_t *triang
         for (int j = 0; j < 3; ++j) p.box.grow(v[j]);
         for (int a = 0; a < 3; ++a) p.c[a] = 0.5 * (p.box.lo[a] + p.box.hi[a]);
         p.tri = (int)kept.size();
+        if ((long long)kept.size() % every == 0) area.push_back(0.5 * nl);
         kept.push_back(f);
-        area.push_back(0.5 * nl);
         B.prims.push_back(p);
     }
     const long long n_kept = (long long)kept.size();

@@ -57,7 +57,7 @@ struct BvhBuild {
     BvhTri *tris = nullptr;
     long long n_tris = 0;
     double lo[3] = {}, hi[3] = {};   // box of the kept triangles
-    double tri_area = 0.0;           // a quarter of them are no larger than this
+    double tri_area = 0.0;           // about a quarter of them are no larger than this
     oceansim_scene_info info{};
 };
 
