@@ -248,8 +248,8 @@ constexpr int kPairBwdLoads = 4;   // ... of a pair backward tile (more would co
 // indices past the end re-read the last pair and are not visited).
 // seg_map: LDS of 2 NT entries.  fn(pair, range, piled): WITH_R loads the
 // pair's range from f.pair_r with the pair (else 0); piled is std::true_type in
-// the rounds for which piled_up(pair, in) is true, given each lane's first
-// pair of the round (in: not past the end) and uniform in a wave.  pre()
+// the rounds for which piled_up(pair) is true, given each lane's first pair of
+// the round and uniform in a wave (asked where every lane has one).  pre()
 // runs once, after the first offset loads are issued and before they are
 // used: independent arithmetic placed there overlaps their latency.
 // Contains barriers.
@@ -294,7 +294,7 @@ __device__ __forceinline__ void for_tile_pairs(const SonarDev &f, int tile, int 
                 for (int u = 0; u < LOADS; ++u)
                     if (k0 + u * NT + tid < total) fn(q[u], rv[u], piled);
             };
-            if (piled_up(q[0], k0 + tid < total))
+            if (__builtin_expect(total - k0 >= NT && piled_up(q[0]), 0))
                 visit(std::true_type{});
             else
                 visit(std::false_type{});
@@ -322,27 +322,24 @@ __device__ __forceinline__ void lds_add(float *p, float v) {
     }
 }
 
-// Whether a wave's adds to the words b of its lanes (with `in`) are better done
+// Whether a wave's adds to the words b of its lanes are better done
 // by ds_add_f32: the rays of a beam on a wall give returns of one bin, and 64
 // lanes on one word take 504 cycles by swaps against 257, eight words of eight
-// lanes 308 against 249, sixteen of four 184 against 241 (run lengths of lanes;
-// shuffled within 3 % of it).  So: some of three lanes finds its word in eight
-// lanes or more.  Looked up once for a round of a thread's pairs: its few
+// lanes 308 against 249, sixteen of four 184 against 241.  So: one of two lanes finds its word in eight
+// lanes or more.  Looked up once for a full round of a thread's pairs: its few
 // instructions for each pair, or counting the lanes that lost a swap, cost
-// scattered returns 5 to 7 % of the tiles' time, this 1 to 3 %.
+// scattered returns 5 to 7 % of the tiles' time, this 1 %.  (Lanes 20 and 44:
+// the middle rays of a beam, whose ranges on a flat wall differ least, are near
+// them whether a beam has 32, 64 or more rays.)
 //
 // k_tile alone, us, by ds_add_f32, by swaps, so: 256 frames of 32768 returns
-// scattered over 256 x 256 bins 75, 42.5, 43.4; in one bin 565, 1033, 565.
+// scattered over 256 x 256 bins 75, 42.5, 42.8; in one bin 565, 1033, 564.
 // Calls of eight frames of 1024 x 1024 bins, 1024 x 128 rays on a flat wall 130,
 // 187, 130; all at one range (a bin per beam) 1468, 2707, 1470.
-__device__ __forceinline__ bool piled_up(unsigned b, bool in) {
-    int most = 0;
-#pragma unroll
-    for (int at = kWave / 4; at < kWave; at += kWave / 4) {
-        const unsigned word = (unsigned)__builtin_amdgcn_readlane((int)b, at);
-        most = max(most, (int)__popcll(__ballot(in && b == word)));
-    }
-    return most >= 8;
+__device__ __forceinline__ bool piled_up(unsigned b) {
+    const unsigned w0 = (unsigned)__builtin_amdgcn_readlane((int)b, 20);
+    const unsigned w1 = (unsigned)__builtin_amdgcn_readlane((int)b, 44);
+    return max((int)__popcll(__ballot(b == w0)), (int)__popcll(__ballot(b == w1))) >= 8;
 }
 
 // Wave-level stream compaction: every wave walks its share of [0, n), queues
@@ -509,7 +506,7 @@ __device__ __forceinline__ void tile_fwd_block(const Src &src, const oceansim_so
                 lds_add(&acc[lb], I);
         },
         []() {},
-        [&](uint2 q, bool in) __attribute__((always_inline)) { return piled_up(matp ? (q.x & 0xffffu) : q.x, in); });
+        [&](uint2 q) __attribute__((always_inline)) { return piled_up(matp ? (q.x & 0xffffu) : q.x); });
     if (f.tile_cemax) {
         __shared__ unsigned s_cemax;
         if (tid == 0) s_cemax = 0u;
@@ -1681,7 +1678,7 @@ __device__ __forceinline__ void pair_bwd_block(const Src &src, const oceansim_so
         }
         if (__builtin_isfinite(xa)) a_alpha += scale_round(xa, s_alpha); else bad_a = true;
         if (__builtin_isfinite(xg)) a_gain += scale_round(xg, s_gain); else bad_g = true;
-    }, []() {}, [](uint2, bool) { return false; });
+    }, []() {}, [](uint2) { return false; });
 
     // 4. workgroup sums (integers: any order; doubles: a fixed order)
     long long lv[3] = {a_alpha, a_gain, a_ssm};
