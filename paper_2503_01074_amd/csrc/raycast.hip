@@ -87,7 +87,7 @@ using cptr = const __attribute__((address_space(4))) T *;
 // Neighbouring tiles meet the same nodes and triangles, so runs of 16 go to one
 // XCD, rotated (a beam's tiles divide a round, and its elevations differ in
 // cost): 8 x (2048 x 1024) rays on a seabed of 130,242 triangles 517 -> 411 us by
-// one traversal per wave, on one of 2 M triangles 1608 -> 1240 us by lanes.
+// one traversal per wave, on one of 2 M triangles 1614 -> 1178 us by lanes.
 struct RayTile {
     int beams, rays;          // tile size
     int b0, r0;               // its first beam and ray

@@ -1792,8 +1792,10 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(6)
 // 111, 52 with 0.6 of the cache accesses.  Two chunks a round keep eight waves
 // on a SIMD (56 registers); four 16.6, 120, 53 (see kFantChunks).  Neighbouring range rows read
 // the same fan lines, so runs of 16 workgroups go to one XCD: 15.8, 107, 43.5
-// (8: 16.6, 108, 44.8; 64: 15.7, 108, 47.4).  What bounds it now is the VALU,
-// mostly the speckle of every bin and the lanes' unequal runs.
+// (8: 16.6, 108, 44.8; 64: 15.7, 108, 47.4).  Neither memory (2.7 TB/s of
+// traffic) nor the VALU (0.37 to 0.54 of its issue slots) bounds it: its waves
+// wait half of their time, on the staged entries' gathers and, where the runs
+// are unequal, on the longest one of a row.
 // ---------------------------------------------------------------------------
 // 64-entry chunks staged per round: two while the rows are short; where a cell
 // has eight fan pixels and more a round of two holds the entries of few lanes,
