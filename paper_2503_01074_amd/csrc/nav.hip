@@ -77,8 +77,8 @@ struct DvlDev {
 // least squares run on full lanes and read the velocity of those ticks alone.
 // One barrier a slab; the buffers that cross it are double (periods, read by
 // the schedule) or triple (beam bits and due bits, read a slab later).
-// 256 ticks x 32768 instances: 78 us, 4.7 TB/s of the 44 B per tick and
-// instance, 3.5 TB/s of the bytes it moves, since only the due ticks' velocities
+// 256 ticks x 32768 instances: 82 us, 4.5 TB/s of the 44 B per tick and
+// instance, 3.8 TB/s of the bytes it moves, since only the due ticks' velocities
 // are read (374 us with one thread per instance walking its ticks: two waves
 // per CU, one tick's loads in flight, the noise drawn under nearly every
 // wave's branch; 95 us with the schedule and the writes in turn, four barriers
